@@ -296,26 +296,22 @@ __device__ __forceinline__ void merge_level(const View& X, const uint32_t* seg0,
 }
 
 // ===========================================================================
-// Keys-only block merge with LDS transposes.
+// Block merge with LDS transposes (64-bit words: mms_device_kt.h).
 //
-// The bitonic block of N = 64*EM keys is sorted with every compare-exchange
+// The bitonic block of N = 64*EM words is sorted with every compare-exchange
 // inside a lane.  Index bits are moved between register and lane positions
 // by two transposes through a wave-private scratch whose 64-word rows are
 // padded (row stride RS), which makes every scratch access conflict-free:
 //   S  (as read)   register = index bits above 6, lane = bits 5..0
-//   T1             register = bits 5..2 (EM=16) or 5..3 (EM=8)
+//   T1             register = bits 5..3
 //   F  (as stored) register 4c+j = position c*256 + 4*lane + j, so each
 //                  lane stores 16-byte chunks and a wave stores 1 KiB runs
-// With EM = 8 index bit 2 is lane bit 0 in F and takes one DPP exchange.
+// Index bit 2 is lane bit 0 in F and takes one DPP exchange.
 // Measured gfx950 rules behind the padding: 32-bit accesses are served 32
 // lanes per cycle over 32 banks, 128-bit accesses 16 lanes per cycle over 64
 // banks.
 // ===========================================================================
 template <int EM> struct Xpose;
-template <> struct Xpose<16> {
-    static constexpr uint32_t RS = 68;
-    static constexpr uint32_t WORDS = 16 * RS;
-};
 template <> struct Xpose<8> {
     static constexpr uint32_t RS = 72;
     static constexpr uint32_t WORDS = 8 * RS;
@@ -369,62 +365,6 @@ __device__ __forceinline__ void cex_u32(uint32_t& lo, uint32_t& hi) {
     hi = max(a, b);
 }
 
-template <int EM>
-__device__ __forceinline__ void reg_stages(uint32_t (&m)[EM]) {
-#pragma unroll
-    for (int d = EM / 2; d >= 1; d >>= 1) {
-#pragma unroll
-        for (int e = 0; e < EM; ++e)
-            if ((e & d) == 0) cex_u32(m[e], m[e | d]);
-    }
-}
-
-// Sort the bitonic block held in layout S; the result is left in layout F.
-template <int EM>
-__device__ __forceinline__ void block_sort_keys(uint32_t (&m)[EM], uint32_t* scr, int lane) {
-    constexpr uint32_t RS = Xpose<EM>::RS;
-    const uint32_t ul = (uint32_t)lane;
-    asm volatile("" ::: "memory");                       // keep the previous block's scratch reads first
-    reg_stages<EM>(m);                                   // index bits 9..6 (EM=16) / 8..6 (EM=8)
-#pragma unroll
-    for (int e = 0; e < EM; ++e) scr[e * RS + ul] = m[e];
-    lds_wave_sync();
-    uint32_t tb;
-    if constexpr (EM == 16) tb = (ul >> 2) * RS + (ul & 3u);   // lane = (bits 9..6, bits 1..0)
-    else tb = (ul >> 3) * RS + (ul & 7u);                       // lane = (bits 8..6, bits 2..0)
-    constexpr uint32_t CS = EM == 16 ? 4u : 8u;                 // stride of the register bits
-#pragma unroll
-    for (int e = 0; e < EM; ++e) m[e] = scr[tb + e * CS];
-    reg_stages<EM>(m);                                   // index bits 5..2 / 5..3
-#pragma unroll
-    for (int e = 0; e < EM; ++e) scr[tb + e * CS] = m[e];
-    lds_wave_sync();
-    const uint32_t fb = (ul >> 4) * RS + 4u * (ul & 15u);
-#pragma unroll
-    for (int c = 0; c < EM / 4; ++c) {
-        const uint4 v = *reinterpret_cast<const uint4*>(scr + fb + (uint32_t)c * 4u * RS);
-        m[4 * c + 0] = v.x;
-        m[4 * c + 1] = v.y;
-        m[4 * c + 2] = v.z;
-        m[4 * c + 3] = v.w;
-    }
-    if constexpr (EM == 8) {                             // index bit 2 = lane bit 0
-        const uint32_t keep_max = (ul & 1u) ? ~0u : 0u;
-        uint32_t o[EM];   // all exchanges first: no wait states between a write and its exchange
-#pragma unroll
-        for (int e = 0; e < EM; ++e) o[e] = (uint32_t)__builtin_amdgcn_mov_dpp((int)m[e], 0xB1, 0xF, 0xF, false);
-#pragma unroll
-        for (int e = 0; e < EM; ++e) m[e] = med3_u32(m[e], o[e], keep_max);
-    }
-#pragma unroll
-    for (int c = 0; c < EM / 4; ++c) {                   // index bits 1..0
-        cex_u32(m[4 * c + 0], m[4 * c + 2]);
-        cex_u32(m[4 * c + 1], m[4 * c + 3]);
-        cex_u32(m[4 * c + 0], m[4 * c + 1]);
-        cex_u32(m[4 * c + 2], m[4 * c + 3]);
-    }
-}
-
 // Store a block held in layout F: chunk c of lane l is block positions
 // p = c*256 + 4l .. p+3.  put4(c, p) stores a whole chunk, put1(c, j, p + j)
 // one position; positions at or past lim are not stored, and whole chunks
@@ -446,193 +386,6 @@ __device__ __forceinline__ void store_block(uint32_t lim, bool vec, int lane, co
             for (int j = 0; j < 4; ++j)
                 if (p + (uint32_t)j < lim) put1(c, j, p + (uint32_t)j);
         }
-    }
-}
-
-// Sinks for a sorted block in layout F: block position t = c*256 + 4*lane + j
-// goes to pos0 + t when t < cnt.  pos0 must be a multiple of 4 for the
-// 16-byte path; `vec` says whether the base pointer allows it.
-struct LdsSinkKeys {
-    uint32_t* y;
-    template <int EM>
-    __device__ __forceinline__ void put_block(uint32_t pos0, uint32_t cnt, const uint32_t (&m)[EM], int lane) const {
-        uint32_t* o = y + pos0;
-        store_block<EM>(
-            cnt, true, lane,
-            [&](int c, uint32_t p) {
-                *reinterpret_cast<uint4*>(o + p) = make_uint4(m[4 * c], m[4 * c + 1], m[4 * c + 2], m[4 * c + 3]);
-            },
-            [&](int c, int j, uint32_t p) { o[p] = m[4 * c + j]; });
-    }
-};
-struct GlobalSinkKeys {
-    uint32_t* y;     // tile output base
-    uint32_t flip;
-    uint32_t lim;    // positions >= lim are not stored
-    bool vec;        // y is 16-byte aligned
-    template <int EM>
-    __device__ __forceinline__ void put_block(uint32_t pos0, uint32_t cnt, const uint32_t (&m)[EM], int lane) const {
-        gu32* g = gptr(y) + pos0;
-        store_block<EM>(
-            min(cnt, lim > pos0 ? lim - pos0 : 0u), vec, lane,
-            [&](int c, uint32_t p) {
-                *reinterpret_cast<gu32x4*>(g + p) =
-                    u32x4{m[4 * c] ^ flip, m[4 * c + 1] ^ flip, m[4 * c + 2] ^ flip, m[4 * c + 3] ^ flip};
-            },
-            [&](int c, int j, uint32_t p) { g[p] = m[4 * c + j] ^ flip; });
-    }
-};
-
-// Number of block positions k = 64 e + lane with a_k <= b_k: the sum of the
-// registers' ballot counts, with no branch (a is non-decreasing and b
-// non-increasing in k, so the positions form a prefix of the block).
-template <int EM>
-__device__ __forceinline__ uint32_t prefix_len(const uint32_t (&a)[EM], const uint32_t (&b)[EM]) {
-    uint32_t u = 0;
-#pragma unroll
-    for (int e = 0; e < EM; ++e) u += (uint32_t)__popcll(__ballot(a[e] <= b[e]));
-    return u;
-}
-
-// Merge outputs [d0, d1) of A = X[aA, aA+la) and B = X[aB, aB+lb) (keys),
-// blocks of N = 64*EM as in merge_pair_range; out_base + d0 must be a
-// multiple of 4.
-template <int EM, class Sink>
-__device__ __forceinline__ void merge_pair_range_keys(const uint32_t* X, uint32_t aA, uint32_t la, uint32_t aB,
-                                                      uint32_t lb, uint32_t d0, uint32_t d1, const Sink& out,
-                                                      uint32_t out_base, uint32_t* scr, int lane) {
-    constexpr uint32_t N = (uint32_t)kWave * EM;
-    if (la == 0 || lb == 0) {
-        // one run is empty (an odd run count at this level, or an empty
-        // piece): the other is already in order; move it in the block layout
-        // the sinks take, 16-byte reads (aA, aB, d0 and N are multiples of
-        // 4; reads past the run stay in the caller's LDS and are not stored)
-        const uint32_t a0 = lb == 0 ? aA : aB;
-        for (uint32_t o = d0; o < d1; o += N) {
-            uint32_t m[EM];
-#pragma unroll
-            for (int c = 0; c < EM / 4; ++c) {
-                const uint4 v = *reinterpret_cast<const uint4*>(X + a0 + o + (uint32_t)c * 256u + 4u * (uint32_t)lane);
-                m[4 * c] = v.x;
-                m[4 * c + 1] = v.y;
-                m[4 * c + 2] = v.z;
-                m[4 * c + 3] = v.w;
-            }
-            out.template put_block<EM>(out_base + o, min(N, d1 - o), m, lane);
-        }
-        return;
-    }
-    if (d0 == 0 && d1 == la + lb && la <= N && lb <= N && la + lb > N) {
-        // The whole pair in one read: A ascending and B descending, each
-        // padded with sentinels to N, form a bitonic sequence of 2N whose
-        // element-wise minimum and maximum halves hold the N smallest keys
-        // and the other la + lb - N (then sentinels), each half bitonic:
-        // two block sorts finish the pair, with no second read.  The reads
-        // stay below the end of B plus N, as in the blocks below.
-        const uint32_t* Ap = X + aA + (uint32_t)lane;
-        const uint32_t* Bp = X + aB + (N - 1u) - (uint32_t)lane;
-        uint32_t a[EM], b[EM], lo[EM], hi[EM];
-#pragma unroll
-        for (int e = 0; e < EM; ++e) {
-            a[e] = Ap[e * kWave];
-            b[e] = Bp[-(e * kWave)];
-        }
-#pragma unroll
-        for (int e = 0; e < EM; ++e) {
-            const uint32_t k = (uint32_t)e * kWave + (uint32_t)lane;
-            const uint32_t ak = k < la ? a[e] : kSentKey;
-            const uint32_t bk = N - 1u - k < lb ? b[e] : kSentKey;
-            lo[e] = min(ak, bk);
-            hi[e] = max(ak, bk);
-        }
-        block_sort_keys<EM>(lo, scr, lane);
-        out.template put_block<EM>(out_base, N, lo, lane);
-        block_sort_keys<EM>(hi, scr, lane);
-        out.template put_block<EM>(out_base + N, la + lb - N, hi, lane);
-        return;
-    }
-    uint32_t p = lds_corank2(X, aA, la, aB, lb, d0, lane);
-    uint32_t q = d0 - p;
-    for (uint32_t o = d0; o < d1; o += N) {
-        uint32_t m[EM];
-        uint32_t u = 0;
-        if (p + N <= la && q + N <= lb) {
-            const uint32_t* Ap = X + aA + p + (uint32_t)lane;
-            const uint32_t* Bp = X + aB + q + (N - 1u) - (uint32_t)lane;
-            uint32_t a[EM], b[EM];
-#pragma unroll
-            for (int e = 0; e < EM; ++e) {      // all reads in flight together
-                a[e] = Ap[e * kWave];
-                b[e] = Bp[-(e * kWave)];
-            }
-#pragma unroll
-            for (int e = 0; e < EM; ++e) m[e] = min(a[e], b[e]);
-            u = prefix_len<EM>(a, b);
-        } else {
-            // near the end of a run: the same reads, then the sentinel for
-            // every position past the run's end, with no branch per element.
-            // Those reads stay below X + (end of the last run) + N, inside
-            // the caller's LDS (the layouts keep at least N words of other
-            // LDS data after each buffer); what they return is discarded.
-            // Keys equal to the sentinel can carry p past la (they are then
-            // indistinguishable from it), so the cursors are capped first.
-            const uint32_t pc = min(p, la), qc = min(q, lb);
-            const uint32_t* Ap = X + aA + pc + (uint32_t)lane;
-            const uint32_t* Bp = X + aB + qc + (N - 1u) - (uint32_t)lane;
-            const uint32_t ra = la - pc, rb = lb - qc;   // elements left in A and B
-            uint32_t a[EM], b[EM];
-#pragma unroll
-            for (int e = 0; e < EM; ++e) {
-                a[e] = Ap[e * kWave];
-                b[e] = Bp[-(e * kWave)];
-            }
-#pragma unroll
-            for (int e = 0; e < EM; ++e) {
-                const uint32_t k = (uint32_t)e * kWave + (uint32_t)lane;
-                a[e] = k < ra ? a[e] : kSentKey;          // still non-decreasing in k
-                b[e] = N - 1u - k < rb ? b[e] : kSentKey;  // still non-increasing in k
-                m[e] = min(a[e], b[e]);
-            }
-            u = prefix_len<EM>(a, b);
-        }
-        block_sort_keys<EM>(m, scr, lane);
-        out.template put_block<EM>(out_base + o, min(N, d1 - o), m, lane);
-        p += u;   // u is a sum of ballot counts: the cursors stay wave-uniform
-        q += N - u;
-    }
-}
-
-// One merge level planned in advance: word 0 of (lvl, wave) holds the
-// wave's main range (pair index in bits 0..3, outputs [d0, d1) in bits
-// 4..17 and 18..31), word 1 a mask of further pairs the wave merges whole.
-// Pair i of level lvl merges segments 2i and 2i+1 (indices into
-// sbeg / plen, clamped to nseg0); the output of pair i starts at its first
-// segment's slot.
-template <int EM, class Sink>
-__device__ __forceinline__ void merge_level_planned(const uint32_t* X, const uint32_t* sbeg, const uint32_t* plen,
-                                                    const uint32_t* plan, uint32_t nseg0, uint32_t lvl,
-                                                    const Sink& out, uint32_t* scr, int wave, int lane) {
-    const uint32_t* pw = plan + 2u * (lvl * 16u + (uint32_t)wave);
-    const uint32_t w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)pw[0]);
-    uint32_t own = (uint32_t)__builtin_amdgcn_readfirstlane((int)pw[1]);
-    auto run = [&](uint32_t i, uint32_t d0, uint32_t d1, bool whole) {
-        const uint32_t g0 = min((2u * i) << lvl, nseg0);
-        const uint32_t g1 = min((2u * i + 1u) << lvl, nseg0);
-        const uint32_t g2 = min((2u * i + 2u) << lvl, nseg0);
-        const uint32_t aA = (uint32_t)__builtin_amdgcn_readfirstlane((int)sbeg[g0]);
-        const uint32_t aB = (uint32_t)__builtin_amdgcn_readfirstlane((int)sbeg[g1]);
-        const uint32_t p0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)plen[g0]);
-        const uint32_t p1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)plen[g1]);
-        const uint32_t p2 = (uint32_t)__builtin_amdgcn_readfirstlane((int)plen[g2]);
-        const uint32_t la = p1 - p0, lb = p2 - p1;
-        if (whole) d1 = la + lb;
-        if (d0 < d1) merge_pair_range_keys<EM>(X, aA, la, aB, lb, d0, d1, out, aA, scr, lane);
-    };
-    run(w0 & 15u, (w0 >> 4) & 0x3FFFu, w0 >> 18, false);
-    while (own) {
-        const uint32_t i = (uint32_t)__builtin_ctz(own);
-        own &= own - 1u;
-        run(i, 0u, 0u, true);
     }
 }
 

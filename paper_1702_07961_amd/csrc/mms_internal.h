@@ -156,10 +156,9 @@ hipError_t launch_merge_pairs(const Phase& ph, const Bufs& b, const RoundArgs& r
                               uint32_t flip, hipStream_t s);
 
 // Keys-only merge round, persistent: `grid` compute units' worth of
-// workgroups walk the phase's tiles.  variant 0: 64x16-key blocks, 8 waves;
-// 1: 64x8-key blocks, 16 waves; 2: 64x8, 8 waves; 3: 64x8, 8 waves, two
-// workgroups per compute unit (registers capped for it; the merge tile must
-// be small enough for two workgroups' LDS); 4: the minBlockHeap merge.
+// workgroups walk the phase's tiles.  variant 0 and 3: 8 waves, 256-key row
+// blocks; 1: 16 waves, 256-key row blocks; 2: 8 waves, 128-key row blocks for
+// merge tiles up to 4096 (256-key ones above); 4: the minBlockHeap merge.
 hipError_t launch_merge_keys(const Phase& ph, const Bufs& b, const RoundArgs& ra, const uint32_t* table,
                              uint32_t flip, unsigned grid, int variant, hipStream_t s);
 

@@ -4,8 +4,8 @@
 // of a round.  A tile's input is the K pieces of its group's runs bounded by
 // the split indices of its first and last output (§4.1).  The pieces are
 // placed at 4-aligned offsets of LDS buffer X and merged pairwise, level by
-// level, with the conflict-free block step of merge_pair_range_keys (log2 K
-// levels: X->Y->X->...); the last level stores straight to memory.
+// level, in row blocks (mms_row_merge.h), log2 K levels: X->Y->X->...; the
+// last level stores straight to memory.
 //
 // Memory latency is hidden by a three-stage pipeline: as tile t starts, the
 // keys of tile t+G are loaded into registers in 16-byte chunks (each thread
@@ -14,14 +14,19 @@
 // built in two steps one tile apart, by three waves besides their share of
 // the merge: wave 0 lays out the pieces of tile t+3G from split-table rows
 // the memory unit copied into LDS one tile earlier, then waves 1 and 2
-// derive the chunk table and the per-level wave plan of tile t+2G from its
-// layout.
+// derive the chunk table and the level items of tile t+2G from its layout.
+//
+// Bound by VALU issue (1.33 wave-instructions per key and round, 75 % of the
+// launch's cycles, LDS busy half of them).  10^8 keys, K = 16, 7424-key tiles:
+// 0.297 ms per launch on average, where wave-wide 512-key blocks with two LDS
+// transposes each took 0.358 ms (the same VALU count, 1.5 times the LDS
+// instructions and 2.4 times the scalar ones, and a longer chain per block).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include "mms_device.h"
 #include "mms_internal.h"
-#include "mms_tile_plan.h"
+#include "mms_row_merge.h"
 
 namespace mms {
 
@@ -145,11 +150,43 @@ __device__ __forceinline__ void fetch_rows_async(const uint32_t* __restrict__ ta
     }
 }
 
-// words of one piece table (with its chunk table)
-constexpr uint32_t kMetaWords = 3u * 17u + kPlanWords + ((kToutKeys + 4u * kMaxFanout) / 64u + 1u + 3u) / 4u;
+// Piece table of a tile: the items of its merge levels, then per piece the
+// source offset src0 (the key in LDS slot P of piece k comes from position
+// src0[k] + P of the group, modulo 2^32), its end send (the slot past its
+// last key) and its first slot sbeg (a multiple of 4; sbeg[Kg]: the end), and
+// the chunk table (the piece whose slots hold slot 64*c).
+struct KeysMeta {
+    uint32_t* items;
+    uint32_t* src0;
+    uint32_t* send;
+    uint32_t* sbeg;
+    uint8_t* cseg;
+};
+constexpr uint32_t kChunkTableWords = ((kToutKeys + 4u * kMaxFanout) / 64u + 1u + 3u) / 4u;
+constexpr uint32_t kMetaWords = (kItemWords + 3u * kMaxFanout + 1u + kChunkTableWords + 3u) / 4u * 4u;
+
+__device__ __forceinline__ KeysMeta keys_meta(uint32_t* at) {
+    uint32_t* s = at + kItemWords;
+    return KeysMeta{at, s, s + kMaxFanout, s + 2u * kMaxFanout, reinterpret_cast<uint8_t*>(s + 3u * kMaxFanout + 1u)};
+}
+
+// Piece layout of a tile of cnt outputs from Kg runs whose split indices
+// s <= e lanes k < Kg hold (run k starts at k*L in its group).
+__device__ __forceinline__ void build_keys_pieces(const KeysMeta& m, uint32_t s, uint32_t e, uint32_t Kg, uint32_t cnt,
+                                                  uint64_t L, int lane) {
+    const PieceLayout pc = piece_layout(s, e, Kg, cnt, lane);
+    if ((uint32_t)lane < Kg) {
+        m.src0[lane] = (uint32_t)((uint64_t)lane * L) + s - pc.sb;
+        m.send[lane] = pc.sb + pc.len;
+        m.sbeg[lane] = pc.sb;
+    }
+    const uint32_t tot =
+        (uint32_t)__builtin_amdgcn_readlane((int)(pc.sb + ((pc.len + 3u) & ~3u)), (int)(Kg - 1u));
+    if (lane == 0) m.sbeg[Kg] = tot;
+}
 
 // Chunk table from the piece layout: largest k < Kg with sbeg[k] <= 64*c.
-__device__ __forceinline__ void build_chunks(const Meta& m, uint32_t Kg, int lane) {
+__device__ __forceinline__ void build_chunks(const KeysMeta& m, uint32_t Kg, int lane) {
     const uint32_t tot_sb = m.sbeg[Kg];
     for (uint32_t c = (uint32_t)lane; c * 64u < tot_sb; c += 64u) {
         uint32_t lo = 0, hi = Kg;
@@ -163,13 +200,13 @@ __device__ __forceinline__ void build_chunks(const Meta& m, uint32_t Kg, int lan
 }
 
 // The whole piece table by one wave (the pipeline's prologue).
-template <int W>
-__device__ __forceinline__ void build_meta(const Meta& m, uint32_t s, uint32_t e, const TileGeo& g, uint64_t L,
-                                          int lane) {
-    build_pieces(m, s, e, g.Kg, g.cnt, L, lane);
+template <int EM>
+__device__ __forceinline__ void build_meta(const KeysMeta& m, uint32_t s, uint32_t e, const TileGeo& g, uint64_t L,
+                                           int lane) {
+    build_keys_pieces(m, s, e, g.Kg, g.cnt, L, lane);
     lds_wave_sync();
     build_chunks(m, g.Kg, lane);
-    build_plan<W>(m, g.Kg, lane);
+    build_items<EM>(m.items, m.sbeg, g.Kg, lane);
 }
 
 }  // namespace
@@ -185,23 +222,23 @@ __global__ __launch_bounds__(W * 64, MINW) void k_merge_keys(Phase ph, Bufs b, R
     const uint64_t tiles = ph.tiles;
     extern __shared__ __align__(16) uint32_t smem[];
     const uint32_t cap = Tout + 4u * K;
-    uint32_t* bufA = smem;
-    uint32_t* bufB = smem + cap;
-    uint32_t* scr = smem + 2 * cap;
-    // the block merge reads up to 64*EM words past a buffer's last run
-    static_assert(W * Xpose<EM>::WORDS >= 64u * EM, "LDS after bufB is shorter than a merge block");
+    // piece tables, level buffers, transpose scratch: the split search reads up
+    // to 16 chunks before or after a buffer
+    uint32_t* mbase = smem;                           // four piece tables of kMetaWords
+    uint32_t* rows = mbase + 4u * kMetaWords;         // wave 0: two split-table rows
+    uint32_t* sent = rows + 2u * kMaxFanout;          // a chunk of the largest key
+    uint32_t* bufA = sent + 4u;
+    uint32_t* bufB = bufA + cap;
+    uint32_t* scr = bufB + cap;
+    static_assert(4u * kMetaWords >= 68u && W * kRowXposeWords >= 68u, "LDS around the level buffers");
     static_assert(W >= 3, "waves 0, 1 and 2 build the piece tables");
-    uint32_t* mbase = scr + W * Xpose<EM>::WORDS;     // four piece tables of kMetaWords
-    auto meta = [&](int which) {
-        uint32_t* mb = mbase + kMetaWords * (uint32_t)which;
-        return Meta{mb, mb + 17, mb + 34, mb + 51, reinterpret_cast<uint8_t*>(mb + 51 + kPlanWords)};
-    };
+    auto meta = [&](int which) { return keys_meta(mbase + kMetaWords * (uint32_t)which); };
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // wave-uniform
     const uint32_t tid = threadIdx.x;
     const uint64_t G = gridDim.x;
-    uint32_t* wscr = scr + (uint32_t)wave * Xpose<EM>::WORDS;
+    uint32_t* wscr = scr + (uint32_t)wave * kRowXposeWords;
 
     uint64_t t = blockIdx.x;
     if (t >= tiles) return;
@@ -210,10 +247,6 @@ __global__ __launch_bounds__(W * 64, MINW) void k_merge_keys(Phase ph, Bufs b, R
     // registers of the prefetch stage: chunks of 4 LDS slots per thread
     u32x4a4 pf_val[PC];
     uint32_t pf_dst[PC];
-    // wave 0: split-table rows of tile t+3G (at loop start), copied in by the
-    // memory unit one tile ahead
-    uint32_t* rows = mbase + 4u * kMetaWords;
-
     // Chunk P (a multiple of 4 in LDS slot coordinates) lies in piece k with
     // sbeg[k] <= P < sbeg[k] + len_k rounded up to 4, so off = P - sbeg[k] <
     // len_k: its first key exists.  Every chunk is one 16-byte load (global
@@ -224,7 +257,7 @@ __global__ __launch_bounds__(W * 64, MINW) void k_merge_keys(Phase ph, Bufs b, R
     // two or more runs hold more than one base tile; a lone run is not loaded
     // at all, its tile is copied from memory).  One load form for every chunk
     // keeps all of a thread's loads in flight together.
-    auto issue_loads = [&](const TileGeo& g, const Meta& m) {
+    auto issue_loads = [&](const TileGeo& g, const KeysMeta& m) {
         if (g.Kg < 2) {
 #pragma unroll
             for (int r = 0; r < PC; ++r) pf_dst[r] = 0xFFFFFFFFu;
@@ -269,7 +302,8 @@ __global__ __launch_bounds__(W * 64, MINW) void k_merge_keys(Phase ph, Bufs b, R
             const uint32_t q = m.src0[k[r]] + P[r];                    // inside the group
             const uint32_t d = q + 4u > glen ? q + 4u - glen : 0u;     // 0..3
             pf_val[r] = *reinterpret_cast<cgu32x4a4*>(gsrc + (q - d));
-            pf_dst[r] = used[r] ? (P[r] | (d << 30)) : 0xFFFFFFFFu;
+            const uint32_t past = P[r] + 4u - min(P[r] + 4u, m.send[k[r]]);   // 0..3 slots past the piece
+            pf_dst[r] = used[r] ? (P[r] | (past << 28) | (d << 30)) : 0xFFFFFFFFu;
         }
     };
     auto store_loads = [&](uint32_t* X) {
@@ -289,7 +323,13 @@ __global__ __launch_bounds__(W * 64, MINW) void k_merge_keys(Phase ph, Bufs b, R
                     v.y = d == 1u ? v.z : v.w;
                     v.z = v.w;
                 }
-                *reinterpret_cast<u32x4*>(X + (pf_dst[r] & 0x3FFFFFFFu)) = v;
+                const uint32_t past = (pf_dst[r] >> 28) & 3u;
+                if (past) {
+                    v.w = kSentKey;
+                    if (past > 1u) v.z = kSentKey;
+                    if (past > 2u) v.y = kSentKey;
+                }
+                *reinterpret_cast<u32x4*>(X + (pf_dst[r] & 0x0FFFFFFFu)) = v;
             }
         }
     };
@@ -309,19 +349,20 @@ __global__ __launch_bounds__(W * 64, MINW) void k_merge_keys(Phase ph, Bufs b, R
         if (wave == 0) {
             uint32_t s, e;
             load_split(table, t, g, L, K, lane, s, e);
-            build_meta<W>(meta(0), s, e, g, L, lane);
+            build_meta<EM>(meta(0), s, e, g, L, lane);
             if (t + G < tiles) {
                 const TileGeo g1 = tile_geo(ph, b, t + G, ra, lL);
                 load_split(table, t + G, g1, L, K, lane, s, e);
-                build_meta<W>(meta(1), s, e, g1, L, lane);
+                build_meta<EM>(meta(1), s, e, g1, L, lane);
                 if (t + 2 * G < tiles) {
                     const TileGeo gp = tile_geo(ph, b, t + 2 * G, ra, lL);
                     load_split(table, t + 2 * G, gp, L, K, lane, s, e);
-                    build_pieces(meta(2), s, e, gp.Kg, gp.cnt, L, lane);
+                    build_keys_pieces(meta(2), s, e, gp.Kg, gp.cnt, L, lane);
                     if (t + 3 * G < tiles) fetch_rows_async(table, t + 3 * G, K, rows, lane);
                 }
             }
         }
+        if (tid < 4u) sent[tid] = kSentKey;
         lds_barrier();
         issue_loads(g, meta(0));
         if (wave == 0) vm_drain();   // the rows copy is older than these loads
@@ -336,8 +377,8 @@ __global__ __launch_bounds__(W * 64, MINW) void k_merge_keys(Phase ph, Bufs b, R
         const TileGeo g = tile_geo(ph, b, t, ra, lL);
         uint32_t* dst = g.dst;
         const uint32_t flip_out = g.final_pass ? flip : 0u;
-        const Meta mc = meta(cur);
-        const Meta mn = meta(nxt(cur));
+        const KeysMeta mc = meta(cur);
+        const KeysMeta mn = meta(nxt(cur));
         const uint64_t tn = t + G, t2 = t + 2 * G;
         const bool has_next = tn < tiles, has2 = t2 < tiles;
 
@@ -353,15 +394,15 @@ __global__ __launch_bounds__(W * 64, MINW) void k_merge_keys(Phase ph, Bufs b, R
             const TileGeo g3 = tile_geo(ph, b, t3, ra, lL);
             uint32_t s3, e3;
             split_from_rows(rows, g3, L, K, lane, s3, e3);
-            build_pieces(meta(nxt(nxt(nxt(cur)))), s3, e3, g3.Kg, g3.cnt, L, lane);
+            build_keys_pieces(meta(nxt(nxt(nxt(cur)))), s3, e3, g3.Kg, g3.cnt, L, lane);
             if (t3 + G < tiles) fetch_rows_async(table, t3 + G, K, rows, lane);
         }
         // waves 1 and 2: chunk table and wave plan of tile t+2G
         if (has2 && (wave == 1 || wave == 2)) {
-            const Meta m2 = meta(nxt(nxt(cur)));
+            const KeysMeta m2 = meta(nxt(nxt(cur)));
             const uint32_t kg2 = tile_geo(ph, b, t2, ra, lL).Kg;
             if (wave == 1) build_chunks(m2, kg2, lane);
-            else build_plan<W>(m2, kg2, lane);
+            else build_items<EM>(m2.items, m2.sbeg, kg2, lane);
         }
         // the next tile's keys go in flight now and land during the last level
         if (has_next) {
@@ -374,7 +415,6 @@ __global__ __launch_bounds__(W * 64, MINW) void k_merge_keys(Phase ph, Bufs b, R
         uint32_t* X = in;
         uint32_t* Y = other;
         const uint64_t obase = g.gb + g.obeg;
-        const int pe = plan_entry<W>(wave);   // balanced over the SIMDs
         uint32_t nlev = 0;
         while ((1u << nlev) < g.Kg) ++nlev;
         // Every tile stores the next tile's keys exactly once, on code every
@@ -387,8 +427,10 @@ __global__ __launch_bounds__(W * 64, MINW) void k_merge_keys(Phase ph, Bufs b, R
         // the top of the next.
         const bool vec = ((uintptr_t)(dst + obase) & 15u) == 0;
         for (uint32_t lvl = 0; lvl + 1u < nlev; ++lvl) {
-            LdsSinkKeys out{Y};
-            merge_level_planned<EM>(X, mc.sbeg, mc.plen, mc.plan, g.Kg, lvl, out, wscr, pe, lane);
+            merge_level_rows<EM, W>(X, mc.items, lvl, sent, wscr, wave, lane,
+                                    [&](uint32_t c, uint32_t k0, uint32_t k1, uint32_t k2, uint32_t k3) {
+                                        *reinterpret_cast<uint4*>(Y + 4u * c) = make_uint4(k0, k1, k2, k3);
+                                    });
             lds_barrier();
             if (lvl == 0) __builtin_amdgcn_s_setprio(0);
             uint32_t* tmp = X; X = Y; Y = tmp;
@@ -399,8 +441,19 @@ __global__ __launch_bounds__(W * 64, MINW) void k_merge_keys(Phase ph, Bufs b, R
         if (g.Kg == 1) {   // a lone run: its tile is already in order
             for (uint32_t j = tid; j < g.cnt; j += NT) gptr(dst)[obase + j] = gptr(g.src)[obase + j] ^ flip_out;
         } else {
-            GlobalSinkKeys out{dst + obase, flip_out, g.cnt, vec};
-            merge_level_planned<EM>(X, mc.sbeg, mc.plen, mc.plan, g.Kg, nlev - 1u, out, wscr, pe, lane);
+            gu32* o = gptr(dst) + obase;
+            merge_level_rows<EM, W>(X, mc.items, nlev - 1u, sent, wscr, wave, lane,
+                                    [&](uint32_t c, uint32_t k0, uint32_t k1, uint32_t k2, uint32_t k3) {
+                                        const u32x4 v{k0 ^ flip_out, k1 ^ flip_out, k2 ^ flip_out, k3 ^ flip_out};
+                                        const uint32_t at = 4u * c;
+                                        if (vec && at + 4u <= g.cnt) {
+                                            *reinterpret_cast<gu32x4*>(o + at) = v;
+                                        } else {
+#pragma unroll
+                                            for (uint32_t j = 0; j < 4u; ++j)
+                                                if (at + j < g.cnt) o[at + j] = v[j];
+                                        }
+                                    });
         }
         lds_barrier();   // publishes the next tile's keys
         __builtin_amdgcn_s_setprio(0);
@@ -413,9 +466,10 @@ __global__ __launch_bounds__(W * 64, MINW) void k_merge_keys(Phase ph, Bufs b, R
     }
 }
 
-// Largest merge tile for which two 8-wave workgroups of 64x8-key blocks fit
-// in one compute unit's 160 KiB of LDS.
-constexpr uint32_t kTout2PerCU = 7424;
+// Merge tiles up to these sizes run with 128-key blocks (where asked for) and
+// with four prefetch chunks per thread.
+constexpr uint32_t kToutSmall = 4096;
+constexpr uint32_t kToutMid = 7424;
 
 static hipError_t allow_lds(const void* f, size_t bytes) {
     return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
@@ -428,9 +482,11 @@ template <int EM, int W, int MINW, uint32_t TMAX>
 static hipError_t launch_variant(const Phase& ph, const Bufs& b, const RoundArgs& ra, const uint32_t* table,
                                  uint32_t flip, unsigned grid, hipStream_t s) {
     constexpr int PC = (int)((TMAX + 4u * kMaxFanout + 4u * W * 64u - 1u) / (4u * W * 64u));
+    // every level's items fit their table (a pair's last item may be partial)
+    static_assert((TMAX + 4u * kMaxFanout) / 4u / kItemChunks<EM> + kMaxFanout / 2u < kItemsPerLevel, "items of a level");
     if (ra.Tout > TMAX) return hipErrorInvalidValue;
     const size_t lds =
-        (2u * (ra.Tout + 4u * ra.K) + W * Xpose<EM>::WORDS + 4u * kMetaWords + 2u * kMaxFanout) * sizeof(uint32_t);
+        (2u * (ra.Tout + 4u * ra.K) + 4u * kMetaWords + 2u * kMaxFanout + 4u + W * kRowXposeWords) * sizeof(uint32_t);
     hipError_t e = allow_lds((const void*)k_merge_keys<EM, W, PC, MINW>, lds);
     if (e != hipSuccess) return e;
     // persistent grid: as many workgroups as fit in the LDS of `grid` CUs
@@ -451,14 +507,12 @@ hipError_t launch_merge_keys(const Phase& ph, const Bufs& b, const RoundArgs& ra
     if (ra.Tout > kToutKeys || ra.K > kMaxFanout || ra.Tout % 4 || ra.L % 4) return hipErrorInvalidValue;
     if (ph.tiles == 0) return hipSuccess;
     if (variant == 4) return launch_merge_heap(ph, b, ra, table, flip, s);
-    if (variant == 1) return launch_variant<8, 16, 1, kToutKeys>(ph, b, ra, table, flip, grid, s);
-    // shape 3 is shape 2 with registers capped for two workgroups per compute
-    // unit, which only merge tiles up to kTout2PerCU leave room for in LDS;
-    // a larger tile runs as shape 2
-    if (variant == 3 && ra.Tout <= kTout2PerCU)
-        return launch_variant<8, 8, 4, kTout2PerCU>(ph, b, ra, table, flip, grid, s);
-    if (variant == 2 || variant == 3) return launch_variant<8, 8, 1, kToutKeys>(ph, b, ra, table, flip, grid, s);
-    return launch_variant<16, 8, 1, kToutKeys>(ph, b, ra, table, flip, grid, s);
+    if (variant == 1) return launch_variant<16, 16, 4, kToutKeys>(ph, b, ra, table, flip, grid, s);
+    // 128-key blocks for small merge tiles (at 2048 keys a row has 64 outputs)
+    if (variant == 2 && ra.Tout <= kToutSmall) return launch_variant<8, 8, 4, kToutSmall>(ph, b, ra, table, flip, grid, s);
+    // fewer prefetch registers where the tile allows
+    if (ra.Tout <= kToutMid) return launch_variant<16, 8, 4, kToutMid>(ph, b, ra, table, flip, grid, s);
+    return launch_variant<16, 8, 4, kToutKeys>(ph, b, ra, table, flip, grid, s);
 }
 
 }  // namespace mms
