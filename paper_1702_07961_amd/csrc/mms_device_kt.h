@@ -204,135 +204,6 @@ __device__ __forceinline__ uint32_t prefix_len_kt(const T (&a)[EM], const T (&b)
     return u;
 }
 
-// LDS sources of a merge level.  Level 0 reads the keys as loaded, each
-// element's tag being its own slot; later levels read keys and 16-bit tags.
-// from(i) gives a cursor at slot i whose at(off) reads slot i + off, so the
-// reads of a block share one address register and constant offsets; raw
-// returns the key and tag unpacked, so a block's reads can all be issued
-// before the first is used.
-struct KtSrcLoaded {
-    using Word = double;
-    const uint32_t* k;
-    struct Cur {
-        const uint32_t* k;
-        uint32_t t0;
-        __device__ __forceinline__ void raw(uint32_t off, uint32_t& key, uint32_t& tag) const {
-            key = k[off];
-            tag = t0 + off;
-        }
-    };
-    __device__ __forceinline__ Cur from(uint32_t i) const { return {k + i, i}; }
-    __device__ __forceinline__ uint32_t corank(uint32_t aA, uint32_t la, uint32_t aB, uint32_t lb, uint32_t d,
-                                               int lane) const {
-        return lds_corank2(k, aA, la, aB, lb, d, lane);
-    }
-    // pairs i .. i+3 (i a multiple of 4)
-    __device__ __forceinline__ void at4(uint32_t i, double* r) const {
-        const uint4 v = *reinterpret_cast<const uint4*>(k + i);
-        r[0] = kt_pack(v.x, i);
-        r[1] = kt_pack(v.y, i + 1u);
-        r[2] = kt_pack(v.z, i + 2u);
-        r[3] = kt_pack(v.w, i + 3u);
-    }
-};
-struct KtSrcTagged {
-    using Word = double;
-    const uint32_t* k;
-    const uint16_t* t;
-    struct Cur {
-        const uint32_t* k;
-        const uint16_t* t;
-        __device__ __forceinline__ void raw(uint32_t off, uint32_t& key, uint32_t& tag) const {
-            key = k[off];
-            tag = t[off];
-        }
-    };
-    __device__ __forceinline__ Cur from(uint32_t i) const { return {k + i, t + i}; }
-    __device__ __forceinline__ uint32_t corank(uint32_t aA, uint32_t la, uint32_t aB, uint32_t lb, uint32_t d,
-                                               int lane) const {
-        return lds_corank2(k, aA, la, aB, lb, d, lane);
-    }
-    __device__ __forceinline__ void at4(uint32_t i, double* r) const {
-        const uint4 v = *reinterpret_cast<const uint4*>(k + i);
-        const uint2 w = *reinterpret_cast<const uint2*>(t + i);
-        r[0] = kt_pack(v.x, w.x & 0xFFFFu);
-        r[1] = kt_pack(v.y, w.x >> 16);
-        r[2] = kt_pack(v.z, w.y & 0xFFFFu);
-        r[3] = kt_pack(v.w, w.y >> 16);
-    }
-};
-
-// Sinks for a sorted block in layout F: block position t = c*256 + 4*lane +
-// j goes to pos0 + t when t < cnt (pos0 a multiple of 4).
-struct KtSinkLds {
-    uint32_t* k;
-    uint16_t* t;
-    template <int EM>
-    __device__ __forceinline__ void put_block(uint32_t pos0, uint32_t cnt, const double (&m)[EM], int lane) const {
-        uint32_t* ok = k + pos0;
-        uint16_t* ot = t + pos0;
-        store_block<EM>(
-            cnt, true, lane,
-            [&](int c, uint32_t p) {
-                const double* r = m + 4 * c;
-                *reinterpret_cast<uint4*>(ok + p) = make_uint4(kt_key(r[0]), kt_key(r[1]), kt_key(r[2]), kt_key(r[3]));
-                // two 16-bit tags per word: the low halves of the low words
-                *reinterpret_cast<uint2*>(ot + p) =
-                    make_uint2(__builtin_amdgcn_perm(kt_lo(r[1]), kt_lo(r[0]), 0x05040100u),
-                               __builtin_amdgcn_perm(kt_lo(r[3]), kt_lo(r[2]), 0x05040100u));
-            },
-            [&](int c, int j, uint32_t p) {
-                ok[p] = kt_key(m[4 * c + j]);
-                ot[p] = (uint16_t)kt_lo(m[4 * c + j]);
-            });
-    }
-};
-// The last level: keys to memory (undoing the signed-key mapping) and each
-// pair's value, gathered from the tile's value slots by its tag.
-struct KtSinkGlobal {
-    uint32_t* k;         // tile output base
-    uint32_t* v;
-    const uint32_t* V;   // LDS values, by slot
-    uint32_t flip;
-    uint32_t lim;        // positions >= lim are not stored
-    bool vec;            // k and v are 16-byte aligned
-    template <int EM>
-    __device__ __forceinline__ void put_block(uint32_t pos0, uint32_t cnt, const double (&m)[EM], int lane) const {
-        gu32* gk = gptr(k) + pos0;
-        gu32* gv = gptr(v) + pos0;
-        store_block<EM>(
-            min(cnt, lim > pos0 ? lim - pos0 : 0u), vec, lane,
-            [&](int c, uint32_t p) {
-                const double* r = m + 4 * c;
-                *reinterpret_cast<gu32x4*>(gk + p) =
-                    u32x4{kt_key(r[0]) ^ flip, kt_key(r[1]) ^ flip, kt_key(r[2]) ^ flip, kt_key(r[3]) ^ flip};
-                *reinterpret_cast<gu32x4*>(gv + p) =
-                    u32x4{V[kt_tag(r[0])], V[kt_tag(r[1])], V[kt_tag(r[2])], V[kt_tag(r[3])]};
-            },
-            [&](int c, int j, uint32_t p) {
-                gk[p] = kt_key(m[4 * c + j]) ^ flip;
-                gv[p] = V[kt_tag(m[4 * c + j])];
-            });
-    }
-};
-
-// A block's candidates: a_e = A[64e] (lane's own offset in A) and b_e =
-// B[64(EM-1-e)], every read issued before any is packed.
-template <int EM, class Cur>
-__device__ __forceinline__ void read_block(const Cur& A, const Cur& B, double (&a)[EM], double (&b)[EM]) {
-    uint32_t ka[EM], ta[EM], kb[EM], tb[EM];
-#pragma unroll
-    for (int e = 0; e < EM; ++e) {
-        A.raw((uint32_t)e * kWave, ka[e], ta[e]);
-        B.raw((uint32_t)(EM - 1 - e) * kWave, kb[e], tb[e]);
-    }
-#pragma unroll
-    for (int e = 0; e < EM; ++e) {
-        a[e] = kt_pack(ka[e], ta[e]);
-        b[e] = kt_pack(kb[e], tb[e]);
-    }
-}
-
 // Merge outputs [d0, d1) of A = X[aA, aA+la) and B = X[aB, aB+lb) in blocks
 // of N = 64*EM words, the 64-bit form of merge_pair_range_keys.  For packed
 // (key, tag) pairs A holds the smaller tags, so the split on keys with A

@@ -7,8 +7,8 @@
 namespace mms {
 
 // Compile-time kernel shapes.  The base case sorts a tile of 64*E*W elements
-// per workgroup (E per lane, W waves); a merge workgroup produces an output
-// tile of Tout elements with W3 waves, 64*EM elements per merge block.
+// per workgroup (E per lane, W waves); a merge workgroup produces output
+// tiles of Tout elements.
 // Base-case shapes, E x W (tile): 0: 8 x 4, 1: 4 x 8, 2: 16 x 2 (2048),
 // 3: 8 x 8, 5: 16 x 4 (4096), 4: 8 x 16, 6: 16 x 8 (8192).  Key-value sorts
 // use shapes 0 and 3.  kT1 is the smallest tile.
@@ -20,9 +20,8 @@ constexpr int base_w(int shape) { return kShapeW[shape]; }
 constexpr uint32_t base_tile(int shape) { return 64u * (uint32_t)base_e(shape) * (uint32_t)base_w(shape); }
 constexpr uint32_t kT1 = 2048;
 static_assert(base_tile(0) == kT1 && base_tile(1) == kT1 && base_tile(2) == kT1, "the smallest tile");
-constexpr int kW3 = 8;      // waves of the key-value merge
 constexpr uint32_t kToutKeys = 8192;   // largest keys-only merge tile
-constexpr uint32_t kToutPairs = 3840;   // two key-value merge workgroups per compute unit
+constexpr uint32_t kToutPairs = 3840;   // four key-value merge workgroups per compute unit
 constexpr uint32_t kMaxFanout = 16;
 
 // The buffers of one segment: its input, its output and its ping-pong

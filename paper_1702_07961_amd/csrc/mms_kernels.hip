@@ -5,7 +5,7 @@
 //   copy        streaming copy, the bandwidth probe
 //
 // The K-way merges of a round (§4.2, §7) are in mms_merge_keys.hip (keys
-// only) and mms_merge_pairs.hip (key-value).
+// only) and mms_merge_words.hip (key-value).
 //
 // Every sorting kernel works on a Phase: a list of tiles, each inside one
 // segment (the plain sort is one segment).  Positions are segment-relative;
