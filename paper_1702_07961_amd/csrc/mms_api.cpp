@@ -2,7 +2,7 @@
 // phase loop (base case, then partition + merge per round), the segmented
 // batch with its hipGraph cache, the tuning table, and the C ABI declared in
 // include/mms.h.  Kernels are launched only through the launchers of
-// mms_kernels.hip and mms_merge_keys.hip.
+// the .hip files.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -385,8 +385,8 @@ int sort_impl(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t
 }
 
 // ---- 64-bit keys (§6.3 also sorts 8-byte integers) ----------------------------
-// Base tiles of kT64Keys keys or kT64Pairs pairs, merge tiles of
-// kTout64Keys / kTout64Pairs, fan-out 16 (MMS64_FANOUT overrides it for
+// Base tiles of kT64Keys keys or kT64Pairs pairs, merge tiles of kTout64,
+// fan-out 16 (MMS64_FANOUT overrides it for
 // experiments: 2, 4, 8 or 16).
 uint32_t fanout64() {
     const char* e = getenv("MMS64_FANOUT");
@@ -407,7 +407,7 @@ Plan64 make_plan64(uint64_t n, bool pairs) {
     p.pairs = pairs;
     p.T = pairs ? mms::kT64Pairs : mms::kT64Keys;
     p.K = fanout64();
-    p.Tout = pairs ? mms::kTout64Pairs : mms::kTout64Keys;
+    p.Tout = mms::kTout64;
     p.rounds = rounds_for(n, p.T, p.K);
     uint64_t L = p.T;
     for (uint32_t r = 0; r < p.rounds; ++r, L *= p.K)

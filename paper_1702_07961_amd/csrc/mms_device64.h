@@ -1,13 +1,13 @@
 // Element kinds of the 64-bit sorts (§6.3 also sorts 8-byte integers) for
-// the generic networks of mms_device.h: the bitonic wave sort, the bitonic
-// merge of a block and the LDS block merge of two runs.
+// the generic networks of mms_device.h (the bitonic wave sort and its merge
+// across waves).
 //
 //   E64   a 64-bit key (unsigned order; signed keys are mapped with
 //         key ^ 2^63 on the way in and back on the way out)
-//   E64T  key and tag.  The tag is the element's slot in the tile as loaded
-//         (the runs sit in LDS in run order), so (key, tag) is the stable
-//         order and every network sorts stably; the values stay in LDS where
-//         they were loaded and are gathered by tag when a tile is stored.
+//   E64T  key and tag.  The tag is the element's slot in the tile as loaded, so
+//         (key, tag) is the stable order and every network sorts stably; the
+//         values stay in LDS where they were loaded and are gathered by tag
+//         when a tile is stored.
 //
 // Every LDS access of the networks moves one element per lane at
 // consecutive element positions (a fixed function of lane and step plus a
@@ -24,7 +24,6 @@ namespace mms {
 
 constexpr uint64_t kSentKey64 = ~0ull;
 constexpr uint32_t kSentTag = 0xFFFFFFFFu;   // above every tag
-constexpr uint64_t kSignFlip64 = 0x8000000000000000ull;
 
 typedef __attribute__((address_space(1))) uint64_t gu64;
 typedef const __attribute__((address_space(1))) uint64_t cgu64;
@@ -41,7 +40,6 @@ struct E64T {
     __device__ static E64T sentinel() { return {kSentKey64, kSentTag}; }
 };
 
-__device__ __forceinline__ bool before(const E64& a, const E64& b) { return a.k < b.k; }
 __device__ __forceinline__ bool before(const E64T& a, const E64T& b) {
     return a.k < b.k || (a.k == b.k && a.t < b.t);
 }
@@ -79,46 +77,5 @@ __device__ __forceinline__ E64 shfl_xor(const E64& e, int m) { return {shfl_xor_
 __device__ __forceinline__ E64T shfl_xor(const E64T& e, int m) {
     return {shfl_xor_u64(e.k, m), shfl_xor_u32(e.t, m)};
 }
-
-// LDS views of a 64-bit key-value merge buffer: key(i) and get(i) read
-// slot i, put(i, e) writes it (the interface merge_level reads and writes
-// through).
-// Key-value merge levels: level 0 reads the keys as loaded, each element's
-// tag being its own slot; later levels read keys and 16-bit tags written by
-// the level before (tile slots stay below 2^16).
-struct LdsKT64Loaded {
-    using El = E64T;
-    uint64_t* k;
-    __device__ __forceinline__ uint64_t key(uint32_t i) const { return k[i]; }
-    __device__ __forceinline__ El get(uint32_t i) const { return {k[i], i}; }
-};
-struct LdsKT64 {
-    using El = E64T;
-    uint64_t* k;
-    uint16_t* t;
-    __device__ __forceinline__ uint64_t key(uint32_t i) const { return k[i]; }
-    __device__ __forceinline__ El get(uint32_t i) const { return {k[i], t[i]}; }
-    __device__ __forceinline__ void put(uint32_t i, const El& e) const {
-        k[i] = e.k;
-        t[i] = (uint16_t)e.t;
-    }
-};
-
-// Memory sink of a tile's last key-value merge level: position i < lim is
-// stored (with the signed-key mapping undone, the value gathered by tag),
-// positions past it are sentinels.
-struct GlobalSinkKT64 {
-    uint64_t* k;
-    uint64_t* v;
-    const uint64_t* V;   // LDS values, by slot as loaded
-    uint64_t flip;
-    uint32_t lim;
-    __device__ __forceinline__ void put(uint32_t i, const E64T& e) const {
-        if (i < lim) {
-            gptr64(k)[i] = e.k ^ flip;
-            gptr64(v)[i] = V[e.t];
-        }
-    }
-};
 
 }  // namespace mms

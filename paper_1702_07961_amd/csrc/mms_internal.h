@@ -170,12 +170,10 @@ hipError_t launch_copy(const uint32_t* in, uint32_t* out, uint64_t n, hipStream_
 
 // ---- 64-bit keys (and 64-bit values): plain sorts only ----------------------
 // Base tiles: kT64Keys keys (8 per lane x 8 waves) or kT64Pairs pairs (8 x
-// 4); merge output tiles kTout64Keys / kTout64Pairs (two workgroups' LDS per
-// compute unit).
+// 4); merge output tiles kTout64 (four workgroups' LDS per compute unit).
 constexpr uint32_t kT64Keys = 4096;
 constexpr uint32_t kT64Pairs = 2048;
-constexpr uint32_t kTout64Keys = 3840;
-constexpr uint32_t kTout64Pairs = 2048;
+constexpr uint32_t kTout64 = 3456;
 
 struct Bufs64 {
     const uint64_t* in_k;

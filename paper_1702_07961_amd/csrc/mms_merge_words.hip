@@ -1,5 +1,5 @@
 // K-way merge rounds of the sorts whose elements are more than a 32-bit key
-// (§4.2, values moving with their keys): stable (32-bit key, value) pairs.
+// (§4.2, §6.3): stable (32-bit key, value) pairs.
 // One workgroup per output tile.
 //
 // A tile's input is the K pieces of its group's runs bounded by the split
@@ -8,10 +8,17 @@
 // the merge tree runs on the words, in place, in row blocks
 // (mms_word_merge.h).  After the last level's reads the values take the words'
 // place in LDS, and each is gathered by its word's tag as the keys are stored.
+//
+// 64-bit keys do not fit a word with their slot, so a tile's words hold the
+// leading 40 bits of its keys' range, and a tile that this did not put in
+// order is set right afterwards (k_merge64 below).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "mms_device.h"
+#include "mms_device64.h"
 #include "mms_device_kt.h"
 #include "mms_internal.h"
 #include "mms_tile_plan.h"
@@ -201,6 +208,288 @@ __global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge_pairs(Phase 
     });
 }
 
+// ===========================================================================
+// 64-bit keys, alone or with 64-bit values.
+//
+// A word holds the leading 40 bits of (key - kmin), kmin and kmax being the
+// tile's smallest and largest key (the ends of its pieces), and the slot in
+// 12.  Words are unique and each piece's are in order, so the merge is exact
+// in the order of the words; it is the order of (key, slot) too unless keys of
+// two pieces agree in those 40 bits and differ below them: about one tile in
+// 40,000 of uniform keys.  So the sorted slots are checked against the keys
+// themselves, which come back into the words' place to be gathered: a tile
+// with an inversion is finished by exchanges of neighbours, which a few short
+// runs of such keys need, and past kFixPasses of them by ranking every element
+// with binary searches in the other pieces.
+// ===========================================================================
+typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+typedef uint64_t u64x2a8 __attribute__((ext_vector_type(2), aligned(8)));
+typedef const __attribute__((address_space(1))) u64x2a8 cgu64x2a8;
+typedef __attribute__((address_space(1))) u64x2 gu64x2;
+
+constexpr int kFixPasses = 8;
+
+// Load the tile's elements (base: the group's first), each wave's share of the
+// steps, up to U in flight: put(first slot of the lane's two, how many of the
+// step's elements are left from there, the elements).  Lanes of a step's last
+// four slots are called with none left.
+template <uint32_t U, int W, class Mid, class Put>
+__device__ __forceinline__ void load_u64(const uint64_t* base, uint32_t glast, const LoadSteps& st, int wave, int lane,
+                                         const Mid& mid, const Put& put) {
+    cgu64* g = gptr64(base);
+    for (uint32_t e0 = (uint32_t)wave; e0 < st.total; e0 += U * W) {
+        u64x2 v[U];
+        uint32_t dst[U], back[U];
+        int left[U];
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {   // steps past the last one load it again and store nothing
+            const uint32_t x = min(e0 + u * W, st.total - 1u);
+            const uint32_t q = (uint32_t)__builtin_amdgcn_readlane((int)st.src, (int)x) + 2u * (uint32_t)lane;
+            const uint32_t qc = min(q, glast);   // the group's last element is read one early
+            back[u] = q - qc;
+            v[u] = *reinterpret_cast<cgu64x2a8*>(g + qc);
+            dst[u] = (uint32_t)__builtin_amdgcn_readlane((int)st.dst, (int)x) + 2u * (uint32_t)lane;
+            const int n = e0 + u * W < st.total ? __builtin_amdgcn_readlane((int)st.cnt, (int)x) : 0;
+            left[u] = 2 * lane < ((n + 3) & ~3) ? n - 2 * lane : -4;
+        }
+        mid(e0);
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u)
+            if (left[u] > -4) put(dst[u], left[u], back[u] ? v[u].y : v[u].x, v[u].y);
+    }
+}
+
+// Minimum (or maximum) over the 16 lanes of each row.
+template <bool MAX>
+__device__ __forceinline__ uint64_t row_extreme(uint64_t x) {
+    auto step = [&](auto ctrl) {
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)x, decltype(ctrl)::value, 0xF, 0xF, false);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(x >> 32), decltype(ctrl)::value, 0xF, 0xF, false);
+        const uint64_t o = ((uint64_t)hi << 32) | lo;
+        x = MAX ? max(x, o) : min(x, o);
+    };
+    step(std::integral_constant<int, 0x121>{});   // row_ror:1
+    step(std::integral_constant<int, 0x122>{});
+    step(std::integral_constant<int, 0x124>{});
+    step(std::integral_constant<int, 0x128>{});
+    return x;
+}
+
+// Bound by VALU issue like the merge above.  Launch average of a sort, against
+// blocks of 64-bit keys in their own order (a compare and four selects per
+// compare-exchange): 10^8 keys 943 -> 662 us; 33,554,467 pairs 674 -> 282 us.
+template <int EM, uint32_t TOUT, int W, bool PAIRS>
+__global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge64(Phase64 ph, Bufs64 b, RoundArgs ra,
+                                                                      const uint32_t* __restrict__ table,
+                                                                      uint64_t flip) {
+    using Items = WordItems<EM, TOUT, W>;
+    constexpr uint32_t CAP = Items::kCap;
+    constexpr uint32_t NT = W * 64u;
+    static_assert(CAP < 4095u, "slots take 12 bits, the sentinel's are all ones");
+    const uint32_t Tout = ra.Tout, K = ra.K;
+    const uint64_t L = ra.L;
+    // split probes read up to 504 bytes before or after the words
+    __shared__ struct __align__(16) {
+        uint32_t scr[W * kWordXposeWords];
+        double X[CAP];
+        double sent[2];
+        uint32_t items[Items::kWords];
+        uint32_t sbeg[kMaxFanout + 1u];
+        uint32_t send[kMaxFanout];
+        uint32_t bad[kFixPasses + 1];
+        uint32_t tags[CAP / 2u];   // the sorted slots, 16 bits each
+    } sm;
+    static_assert(Items::kWords * 4u >= 504u && W * kWordXposeWords * 4u >= 504u, "LDS around the words");
+    double* X = sm.X;
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // wave-uniform
+    const uint32_t tid = threadIdx.x;
+    uint32_t* wscr = sm.scr + (uint32_t)wave * kWordXposeWords;
+    const uint64_t t = blockIdx.x;
+    const uint64_t* src_k = ph.dst_out ? b.ws_k : b.out_k;
+    const uint64_t* src_v = ph.dst_out ? b.ws_v : b.out_v;
+    uint64_t* dst_k = ph.dst_out ? b.out_k : b.ws_k;
+    uint64_t* dst_v = ph.dst_out ? b.out_v : b.ws_v;
+    const uint64_t flip_out = ph.final_pass ? flip : 0ull;
+    const uint32_t grp = (uint32_t)t / (uint32_t)ra.tpg;
+    const uint64_t i = t - (uint64_t)grp * ra.tpg;
+    const uint64_t span = (uint64_t)K * L;
+    const uint64_t gb = (uint64_t)grp * span;
+    const uint64_t glen = min(span, ph.n - gb);
+    const uint32_t Kg = (uint32_t)((glen + L - 1) / L);
+    const uint64_t obeg = i * (uint64_t)Tout;
+    const uint32_t cnt = (uint32_t)min<uint64_t>(Tout, glen - obeg);
+    const uint64_t obase = gb + obeg;
+
+    if (Kg == 1) {   // a lone run: its tile is already in order
+        for (uint32_t j = tid; j < cnt; j += NT) {
+            gptr64(dst_k)[obase + j] = gptr64(src_k)[obase + j] ^ flip_out;
+            if constexpr (PAIRS) gptr64(dst_v)[obase + j] = gptr64(src_v)[obase + j];
+        }
+        return;
+    }
+    uint32_t s = 0, e = 0;
+    if ((uint32_t)lane < Kg) {
+        const uint32_t k = (uint32_t)lane;
+        const uint32_t nk = (uint32_t)min(L, glen - (uint64_t)k * L);
+        // the clamps only guard memory safety; exact splits never trigger them
+        s = i == 0 ? 0u : min(table[t * K + k], nk);
+        e = (obeg + Tout >= glen) ? nk : min(max(table[(t + 1) * K + k], s), nk);
+    }
+    const PieceLayout pc = piece_layout(s, e, Kg, cnt, lane);
+    const LoadSteps st = load_steps(pc, s, Kg, L, lane);
+    uint64_t kmin = ~0ull, kmax = 0;
+    if (pc.len) {   // lanes of non-empty pieces
+        cgu64* p = gptr64(src_k) + (gb + (uint64_t)(uint32_t)lane * L + s);
+        kmin = p[0];
+        kmax = p[pc.len - 1u];
+    }
+    const uint32_t glast = (uint32_t)glen - 2u;   // a group of two runs or more holds more than a base tile
+    uint32_t shift = 0;
+    constexpr uint32_t U = 32 / W;                // steps a wave has in flight
+    load_u64<U, W>(
+        src_k + gb, glast, st, wave, lane,
+        [&](uint32_t e0) {
+            if (e0 == (uint32_t)wave) {
+                // row 0 holds the pieces
+                const uint64_t lo = row_extreme<false>(kmin), hi = row_extreme<true>(kmax);
+                auto first = [](uint64_t x) {
+                    return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32)) << 32) |
+                           (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+                };
+                kmin = first(lo);
+                const uint64_t range = first(hi) - kmin;
+                shift = range >> 40 ? 24u - (uint32_t)__builtin_clzll(range) : 0u;
+            }
+            if (e0 == 0u) {   // wave 0 plans the levels while its first loads are in flight
+                if ((uint32_t)lane < Kg) {
+                    sm.sbeg[lane] = pc.sb;
+                    sm.send[lane] = pc.sb + pc.len;
+                }
+                if (lane <= kFixPasses) sm.bad[lane] = 0u;
+                const uint32_t end =
+                    (uint32_t)__builtin_amdgcn_readlane((int)(pc.sb + ((pc.len + 3u) & ~3u)), (int)(Kg - 1u));
+                if (lane == 0) {
+                    sm.sbeg[Kg] = end;
+                    sm.sent[0] = sm.sent[1] = kt_sentinel();
+                }
+                lds_wave_sync();
+                Items::build(sm.items, sm.sbeg, Kg, lane);
+            }
+        },
+        [&](uint32_t slot, int left, uint64_t k0, uint64_t k1) {
+            auto word = [&](uint64_t key, uint32_t tag) {
+                const uint64_t p = (key - kmin) >> shift;
+                return kt_join(kKtExp | (uint32_t)(p >> 20), ((uint32_t)p << 12) | tag);
+            };
+            const double w0 = left > 0 ? word(k0, slot) : kt_sentinel();
+            const double w1 = left > 1 ? word(k1, slot + 1u) : kt_sentinel();
+            *reinterpret_cast<d2*>(X + slot) = d2{w0, w1};
+        });
+    lds_barrier();
+
+    uint32_t nlev = 0;
+    while ((1u << nlev) < Kg) ++nlev;
+    double m[EM];
+    WordRow o;
+    for (uint32_t lvl = 0;;) {
+        word_merge_level<EM, Items>(X, sm.items, lvl, sm.sent, wscr, wave, lane, m, o);
+        if (++lvl == nlev) break;
+        word_put_lds(X, o, m, lane);
+        lds_barrier();
+    }
+    // the words are read: the keys take their place, by slot
+    word_row_put(o, m, lane, [&](uint32_t c, double a, double z) {
+        sm.tags[c] = (kt_lo(a) & 0xFFFu) | (kt_lo(z) << 16 & 0xFFF0000u);
+    });
+    uint64_t* E = reinterpret_cast<uint64_t*>(X);
+    auto store_lds = [&](uint32_t slot, int left, uint64_t a, uint64_t z) {
+        if (left > 0) *reinterpret_cast<u64x2*>(E + slot) = u64x2{a, z};
+    };
+    load_u64<U, W>(src_k + gb, glast, st, wave, lane, [](uint32_t) {}, store_lds);
+    lds_barrier();
+
+    uint16_t* T = reinterpret_cast<uint16_t*>(sm.tags);
+    auto inverted = [](uint64_t ka, uint32_t a, uint64_t kz, uint32_t z) { return kz < ka || (kz == ka && z < a); };
+    bool bad = false;
+    for (uint32_t c = tid; 2u * c + 1u < cnt; c += NT) {
+        const uint32_t w = sm.tags[c], a = w & 0xFFFFu, z = w >> 16;
+        const uint64_t ka = E[a], kz = E[z];
+        bad = bad || inverted(ka, a, kz, z);
+        if (2u * c + 2u < cnt) {
+            const uint32_t y = T[2u * c + 2u];
+            bad = bad || inverted(kz, z, E[y], y);
+        }
+    }
+    if (__ballot(bad) && lane == 0) sm.bad[0] = 1u;
+    lds_barrier();
+    if (sm.bad[0]) {
+        int pass = 1;
+        for (; pass <= kFixPasses; ++pass) {
+            for (uint32_t par = 0; par < 2u; ++par) {
+                bool moved = false;
+                for (uint32_t c = tid; 2u * c + par + 1u < cnt; c += NT) {
+                    const uint32_t at = 2u * c + par, a = T[at], z = T[at + 1u];
+                    if (inverted(E[a], a, E[z], z)) {
+                        T[at] = (uint16_t)z;
+                        T[at + 1u] = (uint16_t)a;
+                        moved = true;
+                    }
+                }
+                if (__ballot(moved) && lane == 0) sm.bad[pass] = 1u;
+                lds_barrier();
+            }
+            if (!sm.bad[pass]) break;
+        }
+        if (pass > kFixPasses) {
+            // rank = own place in the piece, and for every other piece its
+            // elements before this one (equal keys of earlier pieces are)
+            for (uint32_t slot = tid; slot < sm.sbeg[Kg]; slot += NT) {
+                uint32_t k = 0;
+                while (k + 1u < Kg && sm.sbeg[k + 1u] <= slot) ++k;
+                if (slot >= sm.send[k]) continue;
+                const uint64_t key = E[slot];
+                uint32_t rank = slot - sm.sbeg[k];
+                for (uint32_t j = 0; j < Kg; ++j) {
+                    if (j == k) continue;
+                    const uint32_t beg = sm.sbeg[j];
+                    uint32_t lo = beg, hi = sm.send[j];
+                    while (lo < hi) {
+                        const uint32_t mid = (lo + hi) >> 1;
+                        if (E[mid] < key || (E[mid] == key && j < k)) lo = mid + 1u;
+                        else hi = mid;
+                    }
+                    rank += lo - beg;
+                }
+                T[rank] = (uint16_t)slot;
+            }
+            lds_barrier();
+        }
+    }
+    auto store = [&](uint64_t* out, uint64_t x) {
+        typedef __attribute__((address_space(1))) uint64_t gu64_t;
+        gu64_t* g = (gu64_t*)out + obase;
+        const bool vec = ((uintptr_t)(out + obase) & 15u) == 0;
+        for (uint32_t c = tid; 2u * c < cnt; c += NT) {
+            const uint32_t w = sm.tags[c];
+            if (vec && 2u * c + 1u < cnt) {
+                *reinterpret_cast<gu64x2*>(g + 2u * c) = u64x2{E[w & 0xFFFFu] ^ x, E[w >> 16] ^ x};
+            } else {
+                g[2u * c] = E[w & 0xFFFFu] ^ x;
+                if (2u * c + 1u < cnt) g[2u * c + 1u] = E[w >> 16] ^ x;
+            }
+        }
+    };
+    store(dst_k, flip_out);
+    if constexpr (PAIRS) {   // the values in the keys' place
+        lds_barrier();
+        load_u64<U, W>(src_v + gb, glast, st, wave, lane, [](uint32_t) {}, store_lds);
+        lds_barrier();
+        store(dst_v, 0ull);
+    }
+}
+
 hipError_t launch_merge_pairs(const Phase& ph, const Bufs& b, const RoundArgs& ra, const uint32_t* table,
                               uint32_t flip, hipStream_t s) {
     if (ph.tiles == 0) return hipSuccess;
@@ -218,6 +507,27 @@ hipError_t launch_merge_pairs(const Phase& ph, const Bufs& b, const RoundArgs& r
         hipLaunchKernelGGL((k_merge_pairs<16, kToutPairs, 4>), dim3((unsigned)ph.tiles), dim3(4 * 64), 0, s, ph, b, ra,
                            table, flip);
     return hipGetLastError();
+}
+
+template <bool PAIRS>
+static hipError_t launch64(const Phase64& ph, const Bufs64& b, const RoundArgs& ra, const uint32_t* table,
+                           uint64_t flip, hipStream_t s) {
+    // as for the 32-bit pairs: eight waves of smaller blocks while one
+    // workgroup's latency counts
+    if (ph.tiles <= 1024)
+        hipLaunchKernelGGL((k_merge64<8, kTout64, 8, PAIRS>), dim3((unsigned)ph.tiles), dim3(8 * 64), 0, s, ph, b, ra,
+                           table, flip);
+    else
+        hipLaunchKernelGGL((k_merge64<16, kTout64, 4, PAIRS>), dim3((unsigned)ph.tiles), dim3(4 * 64), 0, s, ph, b, ra,
+                           table, flip);
+    return hipGetLastError();
+}
+
+hipError_t launch_merge64(bool pairs, const Phase64& ph, const Bufs64& b, const RoundArgs& ra, const uint32_t* table,
+                          uint64_t flip, hipStream_t s) {
+    if (ph.tiles == 0) return hipSuccess;
+    if (ra.Tout > kTout64 || ra.Tout % 4 || ra.K > kMaxFanout) return hipErrorInvalidValue;
+    return pairs ? launch64<true>(ph, b, ra, table, flip, s) : launch64<false>(ph, b, ra, table, flip, s);
 }
 
 }  // namespace mms

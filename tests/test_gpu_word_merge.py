@@ -1,7 +1,10 @@
 """Word merge of stable pairs at its edges, against the oracle: short last runs
 of every length around a chunk (2 words), an item (252) and a block (256),
 levels whose pairs need more items than a workgroup has rows (16, several
-passes), lone pieces, and keys equal to the one the sentinel holds.
+passes), lone pieces, and keys equal to the one the sentinel holds.  Then
+64-bit keys that agree in the leading 40 bits of their tile's range and differ
+below, in short runs (finished by exchanges of neighbours) and in long ones
+(by ranking).
 
 A stable order is unique, so the comparison is element by element with no
 tolerance."""
@@ -71,3 +74,34 @@ def test_word_merge_uneven_pairs(mms, weights):
         x[k, :low] >>= np.uint32(1)
         x[k, low:] |= np.uint32(0x80000000)
     check(mms, np.ascontiguousarray(x).reshape(-1))
+
+
+def check64(mms, x):
+    v = np.arange(x.size, dtype=np.uint64) * np.uint64(0x9E3779B97F4A7C15)
+    xd, vd = (torch.from_numpy(a.view(np.int64)).cuda() for a in (x, v))
+    for i64 in (False, True):
+        got = mms.sort64(xd, i64=i64)
+        assert np.array_equal(got.cpu().numpy().view(np.uint64), oracle.sort_u64(x, i64=i64))
+        gk, gv = mms.sort_pairs64(xd, vd, i64=i64)
+        ok, ov = oracle.sort_u64(x, v, i64=i64)
+        assert np.array_equal(gk.cpu().numpy().view(np.uint64), ok)
+        assert np.array_equal(gv.cpu().numpy().view(np.uint64), ov)
+
+
+@pytest.mark.parametrize("n", [4097, 16 * 4096 + 1, 20 * 4096 + 2047])
+@pytest.mark.parametrize("kind", ["short", "equal_and_short", "long", "long_few", "one_low"])
+def test_keys_that_share_a_word(mms, n, kind):
+    low = mmsgen.splitmix64(mmsgen.seed_for(56, 1), n)
+    far = mmsgen.splitmix64(mmsgen.seed_for(56, 2), n)
+    if kind == "short":               # runs of about four keys per tile share their leading bits
+        x = (far % np.uint64(1000) * np.uint64(0x0041000000000000)) | (low & np.uint64(0xFFFF))
+    elif kind == "equal_and_short":   # with equal keys among them
+        x = (far % np.uint64(700) * np.uint64(0x005D000000000000)) | (low & np.uint64(0x3))
+    elif kind == "long":              # every tile spans the range, nearly all keys within 2^20
+        x = np.where(far % np.uint64(64) == 0, far, low & np.uint64(0xFFFFF)).astype(np.uint64)
+    elif kind == "long_few":          # the same with ties
+        x = np.where(far % np.uint64(64) == 0, far, low & np.uint64(0x3F)).astype(np.uint64)
+    else:                             # one small key against all others at the top
+        x = low | np.uint64(0xFFFFFFFFFFF00000)
+        x[n // 2] = 0
+    check64(mms, x)
