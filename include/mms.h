@@ -233,7 +233,7 @@ int mms_segmented_sort(const uint32_t* d_kin, uint32_t* d_kout, const uint32_t* 
  *               sorts one tile per workgroup): 0: 8 x 4, 1: 4 x 8, 2: 16 x 2,
  *               all 2048-key tiles; 3: 8 x 8 and 5: 16 x 4, 4096-key tiles;
  *               4: 8 x 16 and 6: 16 x 8, 8192-key tiles.  Key-value sorts
- *               use shape 3 for shape 4, shapes 0 and 3 as given, else 0.
+ *               use shape 3 for shape 4, shapes 0, 3 and 5 as given, else 0.
  *   flags       0 or MMS_PAIRS, the kind
  * count == 0 restores the built-in default (K = 16, 8192, variant 0, base 0,
  * overridable by MMS_FANOUT / MMS_TOUT / MMS_MERGE_VARIANT /

@@ -31,6 +31,7 @@ VARIANTS = [0, 1, 2, 3, 4]   # 4: the minBlockHeap merge
 # keys per lane x waves: 8x4, 4x8, 16x2 (2048-key tiles), 8x8, 16x4 (4096), 8x16, 16x8 (8192)
 BASES = [0, 1, 2, 3, 4, 5, 6]
 PAIR_BASES = [0, 3]        # key-value base cases: 8x4, 8x8
+PAIR_BASES_16 = [5]   # 16 pairs per lane
 MMS_PAIRS = 0x1
 
 
@@ -82,7 +83,7 @@ def tune_pairs(mms, torch, x_all, min_log2: int, max_log2: int, reps: int, log=p
         x, v, ok, ov = x_all[:n], v_all[:n], ok_all[:n], ov_all[:n]
         best = None
         for K in FANOUTS:
-            for base in PAIR_BASES:
+            for base in PAIR_BASES + PAIR_BASES_16:
                 mms.set_tuning([(64, K, 3840, 0, base, MMS_PAIRS)])
                 ws = torch.empty(max(mms.workspace_bytes(n, pairs=True), 256), dtype=torch.uint8, device="cuda")
                 ms = time_pairs(mms, torch, x, v, ok, ov, ws, max(reps, int(2e6 // n)))

@@ -138,9 +138,9 @@ Tune tune_for(uint64_t n, bool pairs) {
     if (pairs) {
         t.Tout = mms::kToutPairs;
         // key-value base cases: 8 per lane x 4 or 8 waves (8 x 16 sorts pairs
-        // slower than 8 x 8: its LDS holds one workgroup per CU)
+        // slower than 8 x 8: its LDS holds one workgroup per CU) and 16 x 4
         if (t.base == 4) t.base = 3;
-        else if (mms::base_e(t.base) != 8) t.base = 0;
+        else if (mms::base_e(t.base) != 8 && t.base != 5) t.base = 0;
     }
     return t;
 }

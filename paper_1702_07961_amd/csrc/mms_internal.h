@@ -11,7 +11,8 @@ namespace mms {
 // tiles of Tout elements.
 // Base-case shapes, E x W (tile): 0: 8 x 4, 1: 4 x 8, 2: 16 x 2 (2048),
 // 3: 8 x 8, 5: 16 x 4 (4096), 4: 8 x 16, 6: 16 x 8 (8192).  Key-value sorts
-// use shapes 0 and 3.  kT1 is the smallest tile.
+// use shapes 0, 3 and 5.  kT1 is the smallest tile.  Shapes of 16 per lane run
+// the network of mms_tile_net.h.
 constexpr int kBaseShapes = 7;
 constexpr int kShapeE[kBaseShapes] = {8, 4, 16, 8, 8, 16, 16};
 constexpr int kShapeW[kBaseShapes] = {4, 8, 2, 8, 16, 4, 8};

@@ -17,11 +17,12 @@
 #include "mms_device.h"
 #include "mms_device_kt.h"
 #include "mms_internal.h"
+#include "mms_tile_net.h"
 
 namespace mms {
 
 // ===========================================================================
-// Keys-only base case: the W sorted wave chunks are merged by bitonic merges
+// Keys-only base case of the shapes of 4 or 8 per lane: the W sorted wave chunks are merged by bitonic merges
 // across waves instead of LDS block merges.  At level lvl (runs of 2^lvl
 // chunks) the first stage compares every key with its mirror in the paired
 // run (wave w ^ (2^(lvl+1) - 1), lane 63 - l, register E - 1 - e), the next
@@ -268,6 +269,129 @@ __global__ __launch_bounds__(W * 64) void k_tile_sort_pairs(Phase ph, Bufs b, ui
     }
 }
 
+// ===========================================================================
+// Base case of the 16-per-lane shapes: the network of mms_tile_net.h.  Loads
+// and stores are 16-byte chunks in the order of memory (the sorted tile is
+// moved back to it inside each wave).  Keys: bound by VALU issue (93 % of the
+// cycles, LDS 72 % and no bank conflicts); 8192-key tiles of 10^8 keys 271 us
+// (at the counters' clocks), where 8 per lane x 16 waves with every lane and
+// wave distance an exchange of its own takes 457.  Pairs: LDS 76 % of the
+// cycles, VALU 68 %; 4096-pair tiles of 2^27 pairs 608 us, 8 x 8 1448.
+// ===========================================================================
+template <int W>
+__global__ __launch_bounds__(W * 64, 8) void k_tile_net_keys(Phase ph, Bufs b, uint32_t flip) {
+    constexpr uint32_t T = 1024u * W;
+    __shared__ __align__(16) uint32_t X[net_words<uint32_t>(T)];
+    const int lane = threadIdx.x & 63;
+    const uint32_t ul = (uint32_t)lane;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // wave-uniform
+    const TileRef tr = tile_ref(ph, b, blockIdx.x);
+    const uint64_t base = (uint64_t)tr.local * T;
+    const uint32_t cnt = (uint32_t)min<uint64_t>(T, tr.n - base);
+    const uint32_t* in_k = tr.in_k + base;
+    uint32_t* out_k = tr.dst_k + base;
+    const uint32_t flip_out = tr.final_pass ? flip : 0u;
+    const uint32_t at = (uint32_t)wave * 1024u + 4u * ul;
+
+    uint32_t m[kNetRegs];
+#pragma unroll
+    for (uint32_t c = 0; c < 4u; ++c) {
+        const uint32_t j = at + c * 256u;
+        if (j + 4u <= cnt) {
+            const u32x4a4 v = *reinterpret_cast<cgu32x4a4*>(gptr(in_k) + j);
+#pragma unroll
+            for (uint32_t q = 0; q < 4u; ++q) m[4 * c + q] = v[q] ^ flip;
+        } else {
+#pragma unroll
+            for (uint32_t q = 0; q < 4u; ++q) m[4 * c + q] = j + q < cnt ? gptr(in_k)[j + q] ^ flip : kSentKey;
+        }
+    }
+    net_sort<NetKey, W>(X, m, cnt, lane, wave);
+    net_to_memory_order(X, m, ul, (uint32_t)wave);
+    const bool vec = ((uintptr_t)out_k & 15u) == 0;
+    gu32* g = gptr(out_k);
+#pragma unroll
+    for (uint32_t c = 0; c < 4u; ++c) {
+        const uint32_t pos = at + c * 256u;
+        if (vec && pos + 4u <= cnt) {
+            *reinterpret_cast<gu32x4*>(g + pos) = u32x4{m[4 * c] ^ flip_out, m[4 * c + 1] ^ flip_out,
+                                                        m[4 * c + 2] ^ flip_out, m[4 * c + 3] ^ flip_out};
+        } else {
+#pragma unroll
+            for (uint32_t q = 0; q < 4u; ++q)
+                if (pos + q < cnt) g[pos + q] = m[4 * c + q] ^ flip_out;
+        }
+    }
+}
+
+// Pairs: words (key, tile position); the values wait in registers and take the
+// words' place in LDS at the end, to be gathered by tag.
+template <int W>
+__global__ __launch_bounds__(W * 64, 4) void k_tile_net_pairs(Phase ph, Bufs b, uint32_t flip) {
+    constexpr uint32_t T = 1024u * W;
+    __shared__ __align__(16) double X[net_words<double>(T)];
+    const int lane = threadIdx.x & 63;
+    const uint32_t ul = (uint32_t)lane;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // wave-uniform
+    const TileRef tr = tile_ref(ph, b, blockIdx.x);
+    const uint64_t base = (uint64_t)tr.local * T;
+    const uint32_t cnt = (uint32_t)min<uint64_t>(T, tr.n - base);
+    const uint32_t* in_k = tr.in_k + base;
+    const uint32_t* in_v = tr.in_v + base;
+    uint32_t* out_k = tr.dst_k + base;
+    uint32_t* out_v = tr.dst_v + base;
+    const uint32_t flip_out = tr.final_pass ? flip : 0u;
+    const uint32_t at = (uint32_t)wave * 1024u + 4u * ul;
+
+    double m[kNetRegs];
+    u32x4 v[4];
+#pragma unroll
+    for (uint32_t c = 0; c < 4u; ++c) {
+        const uint32_t j = at + c * 256u;
+        if (j + 4u <= cnt) {
+            const u32x4a4 k = *reinterpret_cast<cgu32x4a4*>(gptr(in_k) + j);
+            v[c] = *reinterpret_cast<cgu32x4a4*>(gptr(in_v) + j);
+#pragma unroll
+            for (uint32_t q = 0; q < 4u; ++q) m[4 * c + q] = kt_pack(k[q] ^ flip, j + q);
+        } else {
+#pragma unroll
+            for (uint32_t q = 0; q < 4u; ++q) {
+                m[4 * c + q] = j + q < cnt ? kt_pack(gptr(in_k)[j + q] ^ flip, j + q) : kt_sentinel();
+                v[c][q] = j + q < cnt ? gptr(in_v)[j + q] : 0u;
+            }
+        }
+    }
+    net_sort<NetWord, W>(X, m, cnt, lane, wave);
+    net_to_memory_order(X, m, ul, (uint32_t)wave);
+    uint32_t* V = reinterpret_cast<uint32_t*>(X);
+    lds_barrier();
+#pragma unroll
+    for (uint32_t c = 0; c < 4u; ++c) *reinterpret_cast<u32x4*>(V + at + c * 256u) = v[c];
+    lds_barrier();
+    const bool vec = (((uintptr_t)out_k | (uintptr_t)out_v) & 15u) == 0;
+    gu32* gk = gptr(out_k);
+    gu32* gv = gptr(out_v);
+#pragma unroll
+    for (uint32_t c = 0; c < 4u; ++c) {
+        const uint32_t pos = at + c * 256u;
+        const double* r = m + 4 * c;
+        if (vec && pos + 4u <= cnt) {
+            *reinterpret_cast<gu32x4*>(gk + pos) = u32x4{kt_key(r[0]) ^ flip_out, kt_key(r[1]) ^ flip_out,
+                                                         kt_key(r[2]) ^ flip_out, kt_key(r[3]) ^ flip_out};
+            *reinterpret_cast<gu32x4*>(gv + pos) =
+                u32x4{V[kt_tag(r[0])], V[kt_tag(r[1])], V[kt_tag(r[2])], V[kt_tag(r[3])]};
+        } else {
+#pragma unroll
+            for (uint32_t q = 0; q < 4u; ++q) {
+                if (pos + q < cnt) {
+                    gk[pos + q] = kt_key(r[q]) ^ flip_out;
+                    gv[pos + q] = V[kt_tag(r[q])];
+                }
+            }
+        }
+    }
+}
+
 // One wave per tile of a merge round: the split at the tile's first output.
 // The round reads the buffer its tasks do not write.
 __global__ __launch_bounds__(256) void k_corank_tiles(Phase ph, Bufs b, RoundArgs ra, uint32_t* __restrict__ table) {
@@ -383,20 +507,31 @@ static hipError_t launch_tile_sort_pairs(const Phase& ph, const Bufs& b, uint32_
     return hipGetLastError();
 }
 
+template <int W>
+static hipError_t launch_tile_net(bool pairs, const Phase& ph, const Bufs& b, uint32_t flip, hipStream_t s) {
+    const dim3 grid((unsigned)ph.tiles), block(W * 64);
+    if (pairs) {
+        if constexpr (W == 4) hipLaunchKernelGGL((k_tile_net_pairs<W>), grid, block, 0, s, ph, b, flip);
+        else return hipErrorInvalidValue;
+    } else {
+        hipLaunchKernelGGL((k_tile_net_keys<W>), grid, block, 0, s, ph, b, flip);
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_tile_sort(bool pairs, const Phase& ph, const Bufs& b, uint32_t flip, int base_shape,
                             hipStream_t s) {
     if (ph.tiles == 0) return hipSuccess;
+    if (base_shape == 5) return launch_tile_net<base_w(5)>(pairs, ph, b, flip, s);
     if (!pairs) {
         if (base_shape == 1) return launch_tile_sort_keys<base_e(1), base_w(1)>(ph, b, flip, s);
-        if (base_shape == 2) return launch_tile_sort_keys<base_e(2), base_w(2)>(ph, b, flip, s);
+        if (base_shape == 2) return launch_tile_net<base_w(2)>(false, ph, b, flip, s);
         if (base_shape == 3) return launch_tile_sort_keys<base_e(3), base_w(3)>(ph, b, flip, s);
         if (base_shape == 4) return launch_tile_sort_keys<base_e(4), base_w(4)>(ph, b, flip, s);
-        if (base_shape == 5) return launch_tile_sort_keys<base_e(5), base_w(5)>(ph, b, flip, s);
-        if (base_shape == 6) return launch_tile_sort_keys<base_e(6), base_w(6)>(ph, b, flip, s);
+        if (base_shape == 6) return launch_tile_net<base_w(6)>(false, ph, b, flip, s);
         return launch_tile_sort_keys<base_e(0), base_w(0)>(ph, b, flip, s);
     }
     if (base_shape == 3) return launch_tile_sort_pairs<base_e(3), base_w(3)>(ph, b, flip, s);
-    if (base_shape == 4) return launch_tile_sort_pairs<base_e(4), base_w(4)>(ph, b, flip, s);
     return launch_tile_sort_pairs<base_e(0), base_w(0)>(ph, b, flip, s);
 }
 

@@ -30,31 +30,6 @@
 
 namespace mms {
 
-__device__ __forceinline__ uint32_t min3_u32(uint32_t a, uint32_t b, uint32_t c) {
-    uint32_t d;
-    asm("v_min3_u32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
-    return d;
-}
-__device__ __forceinline__ uint32_t max3_u32(uint32_t a, uint32_t b, uint32_t c) {
-    uint32_t d;
-    asm("v_max3_u32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
-    return d;
-}
-
-// Two stages of a bitonic merge on four elements of a bitonic sequence at
-// equal distances, in six instructions instead of eight.  With lo / hi the
-// smaller and larger of a and c, the first stage leaves {lo, min(b, d)} below
-// {hi, max(b, d)} element by element, so lo <= max(b, d) and hi >= min(b, d):
-// the four results are the minimum and median of (lo, b, d) and the median
-// and maximum of (hi, b, d).
-__device__ __forceinline__ void bitonic4(uint32_t& a, uint32_t& b, uint32_t& c, uint32_t& d) {
-    const uint32_t lo = min(a, c), hi = max(a, c), x = b, y = d;
-    a = min3_u32(lo, x, y);
-    b = med3_u32(lo, x, y);
-    c = med3_u32(hi, x, y);
-    d = max3_u32(hi, x, y);
-}
-
 // Compare-exchange of lanes 4 apart in their row: the lower one keeps the
 // minimum, the upper one the maximum, each in one instruction that writes
 // only the 4-lane banks it concerns.  (A DPP read needs two wait states after
