@@ -385,8 +385,7 @@ int sort_impl(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t
 }
 
 // ---- 64-bit keys (§6.3 also sorts 8-byte integers) ----------------------------
-// Base tiles of kT64Keys keys or kT64Pairs pairs, merge tiles of kTout64,
-// fan-out 16 (MMS64_FANOUT overrides it for
+// Base tiles of kT64 elements, merge tiles of kTout64, fan-out 16 (MMS64_FANOUT overrides it for
 // experiments: 2, 4, 8 or 16).
 uint32_t fanout64() {
     const char* e = getenv("MMS64_FANOUT");
@@ -405,7 +404,7 @@ Plan64 make_plan64(uint64_t n, bool pairs) {
     Plan64 p{};
     p.n = n;
     p.pairs = pairs;
-    p.T = pairs ? mms::kT64Pairs : mms::kT64Keys;
+    p.T = mms::kT64;
     p.K = fanout64();
     p.Tout = mms::kTout64;
     p.rounds = rounds_for(n, p.T, p.K);
@@ -762,7 +761,7 @@ int mms_plan(uint64_t n, uint32_t flags, mms_plan_t* out) {
         out->n = n;
         out->flags = flags;
         out->tile = p.T;
-        out->lanes_per_tile = (p.pairs ? 4 : 8) * 64;
+        out->lanes_per_tile = mms::kT64Waves * 64;
         out->fanout = p.K;
         out->merge_tile = p.Tout;
         out->rounds = n ? p.rounds : 0;

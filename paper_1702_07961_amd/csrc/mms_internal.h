@@ -170,10 +170,10 @@ hipError_t launch_merge_heap(const Phase& ph, const Bufs& b, const RoundArgs& ra
 hipError_t launch_copy(const uint32_t* in, uint32_t* out, uint64_t n, hipStream_t s);
 
 // ---- 64-bit keys (and 64-bit values): plain sorts only ----------------------
-// Base tiles: kT64Keys keys (8 per lane x 8 waves) or kT64Pairs pairs (8 x
-// 4); merge output tiles kTout64 (four workgroups' LDS per compute unit).
-constexpr uint32_t kT64Keys = 4096;
-constexpr uint32_t kT64Pairs = 2048;
+// Base tiles of 16 elements per lane x kT64Waves waves; merge output tiles
+// kTout64 (four workgroups' LDS per compute unit).
+constexpr int kT64Waves = 4;
+constexpr uint32_t kT64 = 1024u * kT64Waves;
 constexpr uint32_t kTout64 = 3456;
 
 struct Bufs64 {

@@ -2,164 +2,137 @@
 // integers): 64-bit keys alone, or stable pairs of 64-bit keys and 64-bit
 // values.  The method is the one of the 32-bit path:
 //
-//   tile_sort64   base case (§4.3): each workgroup sorts a tile in registers
-//                 (a bitonic network per wave, then bitonic merges across
-//                 the waves through LDS)
+//   tile_net64    base case (§4.3): each workgroup sorts a tile of words in
+//                 registers
 //   corank64      partition (§4.1): the exact split of each output tile
 //
-// The K-way merges (§4.2, §7) are in mms_merge_words.hip.
-//
-// Pairs carry (key, tag) through every network, the tag being the element's
-// slot in the tile as loaded, so every step is stable; the values stay in LDS
-// where they were loaded and are gathered by tag when a tile is stored.
+// The K-way merges (§4.2, §7) are in mms_merge_words.hip.  Words carry an
+// element's slot in its tile, so every step is stable; the values never enter
+// the networks and are gathered by slot when a tile is stored.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
-
-#include <type_traits>
 
 #include "mms_corank.h"
 #include "mms_device.h"
 #include "mms_device64.h"
 #include "mms_internal.h"
+#include "mms_order64.h"
+#include "mms_tile_net.h"
 
 namespace mms {
 
-namespace {
-
-// LDS of one exchange buffer of the base case: keys, then (pairs) tags, for
-// T elements
-template <bool PAIRS> constexpr uint32_t xbuf_bytes(uint32_t T) { return T * (PAIRS ? 12u : 8u); }
-// LDS of the base case: (pairs) the values as loaded, then two exchange
-// buffers
-template <bool PAIRS> constexpr uint32_t tile_lds_bytes(uint32_t T) {
-    return (PAIRS ? 8u * T : 0u) + 2u * xbuf_bytes<PAIRS>(T);
-}
-
-}  // namespace
-
 // ===========================================================================
-// Base case.  Wave w loads positions w*CH + e*64 + lane (coalesced) and sorts
-// them in registers; lane l then holds positions l*E .. l*E+E-1 of its wave's
-// run.  Level lvl merges runs of 2^lvl waves: a mirror stage pairs element
-// (lane, e) of wave w with element (63-lane, E-1-e) of wave w ^ (2^(lvl+1)-1),
-// then wave-distance stages pair equal slots, each through LDS, and the
-// in-wave tail finishes.  In LDS element (lane, e) of wave w sits at slot
-// w*CH + e*64 + lane, so every exchange access is 64 consecutive elements.
+// Base case: the network of mms_tile_net.h on words that hold as much of the
+// keys as fits (mms_order64.h).  A thread keeps its keys in registers: they go
+// where the words were to be checked, and again if the tile is sorted twice.
+// 10^8 keys 1244 -> 688 us against a network of 64-bit keys with an exchange for
+// every lane and wave distance (8 per lane x 8 waves); 33,554,467 pairs 774 ->
+// 310 us against one of keys and tags (2048-pair tiles).
 // ===========================================================================
-template <int E, int W, bool PAIRS>
-__global__ __launch_bounds__(W * 64) void k_tile_sort64(Phase64 ph, Bufs64 b, uint64_t flip) {
-    using El = std::conditional_t<PAIRS, E64T, E64>;
-    constexpr uint32_t CH = 64u * E;
-    constexpr uint32_t T = CH * W;
-    extern __shared__ __align__(16) uint64_t smem64[];
-    uint64_t* V = smem64;                                       // pairs: values by slot
-    uint8_t* xbase = reinterpret_cast<uint8_t*>(smem64 + (PAIRS ? T : 0u));
-
+template <int W, bool PAIRS>
+__global__ __launch_bounds__(W * 64, 3) void k_tile_net64(Phase64 ph, Bufs64 b, uint64_t flip) {
+    constexpr uint32_t T = 1024u * W, NT = W * 64u;
+    static_assert(T <= 1u << kSlotBits, "slots");
+    __shared__ struct __align__(16) {
+        double X[net_words<double>(T)];
+        uint32_t tags[T / 2u];   // the sorted slots, 16 bits each
+        uint64_t lo[W], hi[W];
+        Order64<W> order;
+    } sm;
     const int lane = threadIdx.x & 63;
-    const uint32_t ul = (uint32_t)lane;
+    const uint32_t ul = (uint32_t)lane, tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint64_t base = (uint64_t)blockIdx.x * T;
     const uint32_t cnt = (uint32_t)min<uint64_t>(T, ph.n - base);
-    uint64_t* out_k = (ph.dst_out ? b.out_k : b.ws_k) + base;
-    uint64_t* out_v = PAIRS ? (ph.dst_out ? b.out_v : b.ws_v) + base : nullptr;
     const uint64_t flip_out = ph.final_pass ? flip : 0ull;
-
-    // the wave sorts any arrangement of its keys, so each lane loads two
-    // consecutive elements per 16-byte load (chunk c: positions c*128 +
-    // 2*lane, +1); a pair's tag is its own tile position
-    typedef uint64_t v2u64 __attribute__((ext_vector_type(2)));
-    typedef const __attribute__((address_space(1))) v2u64 cgv2u64;
-    El r[E];
-    const uint64_t* in_k = b.in_k + base;
-    const uint64_t* in_v = PAIRS ? b.in_v + base : b.in_k + base;
-    const bool vec_in = ((((uintptr_t)in_k) | (uintptr_t)in_v) & 15u) == 0;
+    typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+    typedef uint64_t u64x2a8 __attribute__((ext_vector_type(2), aligned(8)));
+    typedef const __attribute__((address_space(1))) u64x2a8 cgu64x2a8;
+    // elements at + 128c and the next one are the thread's (c < 8)
+    const uint32_t at = (uint32_t)wave * 1024u + 2u * ul;
+    auto load = [&](const uint64_t* in, uint64_t (&r)[kNetRegs], uint64_t x) {
 #pragma unroll
-    for (uint32_t c = 0; c < (uint32_t)E / 2u; ++c) {
-        const uint32_t j = (uint32_t)wave * CH + c * 128u + 2u * ul;
-        if (vec_in && j + 2u <= cnt) {
-            const v2u64 k = *reinterpret_cast<cgv2u64*>(gptr64(in_k) + j);
-            if constexpr (PAIRS) {
-                const v2u64 v = *reinterpret_cast<cgv2u64*>(gptr64(in_v) + j);
-                r[2 * c] = El{k[0] ^ flip, j};
-                r[2 * c + 1] = El{k[1] ^ flip, j + 1u};
-                V[j] = v[0];
-                V[j + 1] = v[1];
+        for (uint32_t c = 0; c < 8u; ++c) {
+            const uint32_t j = at + 128u * c;
+            if (j + 2u <= cnt) {
+                const u64x2a8 v = *reinterpret_cast<cgu64x2a8*>(gptr64(in) + base + j);
+                r[2 * c] = v.x ^ x;
+                r[2 * c + 1] = v.y ^ x;
             } else {
-                r[2 * c] = El{k[0] ^ flip};
-                r[2 * c + 1] = El{k[1] ^ flip};
+                r[2 * c] = j < cnt ? gptr64(in)[base + j] ^ x : 0ull;
+                r[2 * c + 1] = 0ull;
             }
-        } else {
-#pragma unroll
-            for (uint32_t q = 0; q < 2u; ++q) {
-                const uint32_t jq = j + q;
-                if (jq < cnt) {
-                    if constexpr (PAIRS) {
-                        r[2 * c + q] = El{gptr64(in_k)[jq] ^ flip, jq};
-                        V[jq] = gptr64(in_v)[jq];
-                    } else {
-                        r[2 * c + q] = El{gptr64(in_k)[jq] ^ flip};
-                    }
-                } else {
-                    r[2 * c + q] = El::sentinel();
-                }
-            }
-        }
-    }
-    wave_sort_blocked<E>(r, lane);
-
-    uint32_t buf = 0;
-    auto exchange = [&](int pw, bool mirror, bool want_first) {
-        uint8_t* X = xbase + buf * xbuf_bytes<PAIRS>(T);
-        buf ^= 1u;
-        uint64_t* xk = reinterpret_cast<uint64_t*>(X);
-        uint32_t* xt = reinterpret_cast<uint32_t*>(xk + T);
-        const uint32_t me = (uint32_t)wave * CH;
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const uint32_t slot = me + (uint32_t)e * 64u + ul;
-            xk[slot] = r[e].k;
-            if constexpr (PAIRS) xt[slot] = r[e].t;
-        }
-        lds_barrier();
-        const uint32_t them = (uint32_t)pw * CH;
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const uint32_t slot = them + (mirror ? (uint32_t)(E - 1 - e) * 64u + (63u - ul) : (uint32_t)e * 64u + ul);
-            El o;
-            if constexpr (PAIRS) o = El{xk[slot], xt[slot]};
-            else o = El{xk[slot]};
-            r[e] = pick(r[e], o, want_first);
         }
     };
+    uint64_t* E = reinterpret_cast<uint64_t*>(sm.X);
+    auto put = [&](const uint64_t (&r)[kNetRegs]) {
 #pragma unroll
-    for (int lvl = 0; (1 << lvl) < W; ++lvl) {
-        const int gw = 1 << lvl;
-        exchange(wave ^ (2 * gw - 1), true, (wave & gw) == 0);
-#pragma unroll
-        for (int dw = gw >> 1; dw >= 1; dw >>= 1) exchange(wave ^ dw, false, (wave & dw) == 0);
-        wave_merge_tail<E>(r, lane);
-    }
+        for (uint32_t c = 0; c < 8u; ++c) *reinterpret_cast<u64x2*>(E + at + 128u * c) = u64x2{r[2 * c], r[2 * c + 1]};
+    };
 
-    // lane l holds tile positions wave*CH + l*E .. + E-1: pairs of 16 bytes
-    const uint32_t p0 = (uint32_t)wave * CH + ul * (uint32_t)E;
-    const bool vec = ((((uintptr_t)out_k) | (uintptr_t)(PAIRS ? out_v : out_k)) & 15u) == 0;
-    typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
-    typedef __attribute__((address_space(1))) u64x2 gu64x2;
+    uint64_t key[kNetRegs];
+    load(b.in_k, key, flip);
+    uint64_t kmin = ~0ull, kmax = 0;
 #pragma unroll
-    for (int e = 0; e < E; e += 2) {
-        const uint32_t pos = p0 + (uint32_t)e;
-        if (vec && pos + 2u <= cnt) {
-            *reinterpret_cast<gu64x2*>(gptr64(out_k) + pos) = u64x2{r[e].k ^ flip_out, r[e + 1].k ^ flip_out};
-            if constexpr (PAIRS) *reinterpret_cast<gu64x2*>(gptr64(out_v) + pos) = u64x2{V[r[e].t], V[r[e + 1].t]};
-        } else {
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                if (pos + (uint32_t)j < cnt) {
-                    gptr64(out_k)[pos + j] = r[e + j].k ^ flip_out;
-                    if constexpr (PAIRS) gptr64(out_v)[pos + j] = V[r[e + j].t];
-                }
-            }
+    for (uint32_t r = 0; r < kNetRegs; ++r) {
+        const bool own = at + 128u * (r >> 1) + (r & 1u) < cnt;
+        kmin = own ? min(kmin, key[r]) : kmin;
+        kmax = own ? max(kmax, key[r]) : kmax;
+    }
+    kmin = row_extreme<false>(kmin);
+    kmax = row_extreme<true>(kmax);
+    {
+        const uint64_t lo = min(min(lane_u64(kmin, 0), lane_u64(kmin, 16)), min(lane_u64(kmin, 32), lane_u64(kmin, 48)));
+        const uint64_t hi = max(max(lane_u64(kmax, 0), lane_u64(kmax, 16)), max(lane_u64(kmax, 32), lane_u64(kmax, 48)));
+        if (lane == 0) {
+            sm.lo[wave] = lo;
+            sm.hi[wave] = hi;
         }
+        if (tid == 0) sm.order.bad = 0u;
+    }
+    lds_barrier();
+    kmin = sm.lo[0];
+    kmax = sm.hi[0];
+#pragma unroll
+    for (int w = 1; w < W; ++w) {
+        kmin = min(kmin, sm.lo[w]);
+        kmax = max(kmax, sm.hi[w]);
+    }
+    kmin = lane_u64(kmin, 0);   // the same in every lane
+    const uint32_t shift = prefix_shift(lane_u64(kmax, 0) - kmin);
+
+    double m[kNetRegs];
+#pragma unroll
+    for (uint32_t r = 0; r < kNetRegs; ++r) {
+        const uint32_t slot = at + 128u * (r >> 1) + (r & 1u);
+        m[r] = slot < cnt ? order_word((key[r] - kmin) >> shift, slot) : kt_sentinel();
+    }
+    for (bool exact = false;;) {
+        net_sort<NetWord, W>(sm.X, m, cnt, lane, wave);
+        uint32_t* t = sm.tags + (uint32_t)wave * 512u + ul * 8u;   // layout A: 16 positions in a row
+#pragma unroll
+        for (uint32_t r = 0; r < 8u; ++r) t[r] = word_slot(m[2 * r]) | word_slot(m[2 * r + 1]) << 16;
+        lds_barrier();
+        put(key);
+        lds_barrier();
+        if (exact || shift == 0u || sm.order.ordered(E, sm.tags, cnt, tid)) break;
+        exact = true;
+        sm.order.template second_words<T / NT>(E, sm.tags, cnt, kmin, shift, tid);
+        lds_barrier();
+#pragma unroll
+        for (uint32_t r = 0; r < kNetRegs; ++r) {
+            const uint32_t slot = at + 128u * (r >> 1) + (r & 1u);
+            m[r] = slot < cnt ? sm.X[slot] : kt_sentinel();
+        }
+        lds_barrier();
+    }
+    store_by_tags<NT>((ph.dst_out ? b.out_k : b.ws_k) + base, E, sm.tags, cnt, flip_out, tid);
+    if constexpr (PAIRS) {
+        load(b.in_v, key, 0ull);
+        lds_barrier();
+        put(key);
+        lds_barrier();
+        store_by_tags<NT>((ph.dst_out ? b.out_v : b.ws_v) + base, E, sm.tags, cnt, 0ull, tid);
     }
 }
 
@@ -189,27 +162,12 @@ __global__ __launch_bounds__(256) void k_corank_tiles64(Phase64 ph, Bufs64 b, Ro
 // ===========================================================================
 // Launchers
 // ===========================================================================
-static hipError_t allow_lds64(const void* f, size_t bytes) {
-    return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-}
-
 hipError_t launch_tile_sort64(bool pairs, const Phase64& ph, const Bufs64& b, uint64_t flip, hipStream_t s) {
     if (ph.tiles == 0) return hipSuccess;
-    if (pairs) {
-        constexpr int E = 8, W = 4;
-        static_assert(64u * E * W == kT64Pairs, "pairs base tile");
-        const size_t lds = tile_lds_bytes<true>(kT64Pairs);
-        hipError_t e = allow_lds64((const void*)k_tile_sort64<E, W, true>, lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_tile_sort64<E, W, true>), dim3((unsigned)ph.tiles), dim3(W * 64), lds, s, ph, b, flip);
-    } else {
-        constexpr int E = 8, W = 8;
-        static_assert(64u * E * W == kT64Keys, "keys base tile");
-        const size_t lds = tile_lds_bytes<false>(kT64Keys);
-        hipError_t e = allow_lds64((const void*)k_tile_sort64<E, W, false>, lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_tile_sort64<E, W, false>), dim3((unsigned)ph.tiles), dim3(W * 64), lds, s, ph, b, flip);
-    }
+    constexpr int W = kT64Waves;
+    const dim3 grid((unsigned)ph.tiles), block(W * 64);
+    if (pairs) hipLaunchKernelGGL((k_tile_net64<W, true>), grid, block, 0, s, ph, b, flip);
+    else hipLaunchKernelGGL((k_tile_net64<W, false>), grid, block, 0, s, ph, b, flip);
     return hipGetLastError();
 }
 

@@ -21,6 +21,7 @@
 #include "mms_device64.h"
 #include "mms_device_kt.h"
 #include "mms_internal.h"
+#include "mms_order64.h"
 #include "mms_tile_plan.h"
 #include "mms_word_merge.h"
 
@@ -211,23 +212,15 @@ __global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge_pairs(Phase 
 // ===========================================================================
 // 64-bit keys, alone or with 64-bit values.
 //
-// A word holds the leading 40 bits of (key - kmin), kmin and kmax being the
-// tile's smallest and largest key (the ends of its pieces), and the slot in
-// 12.  Words are unique and each piece's are in order, so the merge is exact
-// in the order of the words; it is the order of (key, slot) too unless keys of
-// two pieces agree in those 40 bits and differ below them: about one tile in
-// 40,000 of uniform keys.  So the sorted slots are checked against the keys
-// themselves, which come back into the words' place to be gathered: a tile
-// with an inversion is finished by exchanges of neighbours, which a few short
-// runs of such keys need, and past kFixPasses of them by ranking every element
-// with binary searches in the other pieces.
+// The words hold as much of the keys as fits (mms_order64.h); words are unique
+// and each piece's are in order, so the merge is exact in the order of the
+// words.  The keys then come back into the words' place, to be checked and
+// gathered.  A tile that is not in order merges its second words: a piece's are
+// in order too, so its levels and items are the same.
 // ===========================================================================
 typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
 typedef uint64_t u64x2a8 __attribute__((ext_vector_type(2), aligned(8)));
 typedef const __attribute__((address_space(1))) u64x2a8 cgu64x2a8;
-typedef __attribute__((address_space(1))) u64x2 gu64x2;
-
-constexpr int kFixPasses = 8;
 
 // Load the tile's elements (base: the group's first), each wave's share of the
 // steps, up to U in flight: put(first slot of the lane's two, how many of the
@@ -259,25 +252,9 @@ __device__ __forceinline__ void load_u64(const uint64_t* base, uint32_t glast, c
     }
 }
 
-// Minimum (or maximum) over the 16 lanes of each row.
-template <bool MAX>
-__device__ __forceinline__ uint64_t row_extreme(uint64_t x) {
-    auto step = [&](auto ctrl) {
-        const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)x, decltype(ctrl)::value, 0xF, 0xF, false);
-        const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(x >> 32), decltype(ctrl)::value, 0xF, 0xF, false);
-        const uint64_t o = ((uint64_t)hi << 32) | lo;
-        x = MAX ? max(x, o) : min(x, o);
-    };
-    step(std::integral_constant<int, 0x121>{});   // row_ror:1
-    step(std::integral_constant<int, 0x122>{});
-    step(std::integral_constant<int, 0x124>{});
-    step(std::integral_constant<int, 0x128>{});
-    return x;
-}
-
 // Bound by VALU issue like the merge above.  Launch average of a sort, against
 // blocks of 64-bit keys in their own order (a compare and four selects per
-// compare-exchange): 10^8 keys 943 -> 662 us; 33,554,467 pairs 674 -> 282 us.
+// compare-exchange): 10^8 keys 943 -> 680 us; 33,554,467 pairs 674 -> 292 us.
 template <int EM, uint32_t TOUT, int W, bool PAIRS>
 __global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge64(Phase64 ph, Bufs64 b, RoundArgs ra,
                                                                       const uint32_t* __restrict__ table,
@@ -285,7 +262,7 @@ __global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge64(Phase64 ph
     using Items = WordItems<EM, TOUT, W>;
     constexpr uint32_t CAP = Items::kCap;
     constexpr uint32_t NT = W * 64u;
-    static_assert(CAP < 4095u, "slots take 12 bits, the sentinel's are all ones");
+    static_assert(CAP < 1u << kSlotBits, "slots");
     const uint32_t Tout = ra.Tout, K = ra.K;
     const uint64_t L = ra.L;
     // split probes read up to 504 bytes before or after the words
@@ -296,7 +273,7 @@ __global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge64(Phase64 ph
         uint32_t items[Items::kWords];
         uint32_t sbeg[kMaxFanout + 1u];
         uint32_t send[kMaxFanout];
-        uint32_t bad[kFixPasses + 1];
+        Order64<W> order;
         uint32_t tags[CAP / 2u];   // the sorted slots, 16 bits each
     } sm;
     static_assert(Items::kWords * 4u >= 504u && W * kWordXposeWords * 4u >= 504u, "LDS around the words");
@@ -353,140 +330,65 @@ __global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge64(Phase64 ph
         [&](uint32_t e0) {
             if (e0 == (uint32_t)wave) {
                 // row 0 holds the pieces
-                const uint64_t lo = row_extreme<false>(kmin), hi = row_extreme<true>(kmax);
-                auto first = [](uint64_t x) {
-                    return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32)) << 32) |
-                           (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
-                };
-                kmin = first(lo);
-                const uint64_t range = first(hi) - kmin;
-                shift = range >> 40 ? 24u - (uint32_t)__builtin_clzll(range) : 0u;
+                kmax = lane_u64(row_extreme<true>(kmax), 0);
+                kmin = lane_u64(row_extreme<false>(kmin), 0);
+                shift = prefix_shift(kmax - kmin);
             }
             if (e0 == 0u) {   // wave 0 plans the levels while its first loads are in flight
                 if ((uint32_t)lane < Kg) {
                     sm.sbeg[lane] = pc.sb;
                     sm.send[lane] = pc.sb + pc.len;
                 }
-                if (lane <= kFixPasses) sm.bad[lane] = 0u;
                 const uint32_t end =
                     (uint32_t)__builtin_amdgcn_readlane((int)(pc.sb + ((pc.len + 3u) & ~3u)), (int)(Kg - 1u));
                 if (lane == 0) {
                     sm.sbeg[Kg] = end;
                     sm.sent[0] = sm.sent[1] = kt_sentinel();
+                    sm.order.bad = 0u;
                 }
                 lds_wave_sync();
                 Items::build(sm.items, sm.sbeg, Kg, lane);
             }
         },
         [&](uint32_t slot, int left, uint64_t k0, uint64_t k1) {
-            auto word = [&](uint64_t key, uint32_t tag) {
-                const uint64_t p = (key - kmin) >> shift;
-                return kt_join(kKtExp | (uint32_t)(p >> 20), ((uint32_t)p << 12) | tag);
-            };
-            const double w0 = left > 0 ? word(k0, slot) : kt_sentinel();
-            const double w1 = left > 1 ? word(k1, slot + 1u) : kt_sentinel();
+            const double w0 = left > 0 ? order_word((k0 - kmin) >> shift, slot) : kt_sentinel();
+            const double w1 = left > 1 ? order_word((k1 - kmin) >> shift, slot + 1u) : kt_sentinel();
             *reinterpret_cast<d2*>(X + slot) = d2{w0, w1};
         });
     lds_barrier();
 
     uint32_t nlev = 0;
     while ((1u << nlev) < Kg) ++nlev;
-    double m[EM];
-    WordRow o;
-    for (uint32_t lvl = 0;;) {
-        word_merge_level<EM, Items>(X, sm.items, lvl, sm.sent, wscr, wave, lane, m, o);
-        if (++lvl == nlev) break;
-        word_put_lds(X, o, m, lane);
-        lds_barrier();
-    }
-    // the words are read: the keys take their place, by slot
-    word_row_put(o, m, lane, [&](uint32_t c, double a, double z) {
-        sm.tags[c] = (kt_lo(a) & 0xFFFu) | (kt_lo(z) << 16 & 0xFFF0000u);
-    });
     uint64_t* E = reinterpret_cast<uint64_t*>(X);
     auto store_lds = [&](uint32_t slot, int left, uint64_t a, uint64_t z) {
         if (left > 0) *reinterpret_cast<u64x2*>(E + slot) = u64x2{a, z};
     };
-    load_u64<U, W>(src_k + gb, glast, st, wave, lane, [](uint32_t) {}, store_lds);
-    lds_barrier();
-
-    uint16_t* T = reinterpret_cast<uint16_t*>(sm.tags);
-    auto inverted = [](uint64_t ka, uint32_t a, uint64_t kz, uint32_t z) { return kz < ka || (kz == ka && z < a); };
-    bool bad = false;
-    for (uint32_t c = tid; 2u * c + 1u < cnt; c += NT) {
-        const uint32_t w = sm.tags[c], a = w & 0xFFFFu, z = w >> 16;
-        const uint64_t ka = E[a], kz = E[z];
-        bad = bad || inverted(ka, a, kz, z);
-        if (2u * c + 2u < cnt) {
-            const uint32_t y = T[2u * c + 2u];
-            bad = bad || inverted(kz, z, E[y], y);
-        }
-    }
-    if (__ballot(bad) && lane == 0) sm.bad[0] = 1u;
-    lds_barrier();
-    if (sm.bad[0]) {
-        int pass = 1;
-        for (; pass <= kFixPasses; ++pass) {
-            for (uint32_t par = 0; par < 2u; ++par) {
-                bool moved = false;
-                for (uint32_t c = tid; 2u * c + par + 1u < cnt; c += NT) {
-                    const uint32_t at = 2u * c + par, a = T[at], z = T[at + 1u];
-                    if (inverted(E[a], a, E[z], z)) {
-                        T[at] = (uint16_t)z;
-                        T[at + 1u] = (uint16_t)a;
-                        moved = true;
-                    }
-                }
-                if (__ballot(moved) && lane == 0) sm.bad[pass] = 1u;
-                lds_barrier();
-            }
-            if (!sm.bad[pass]) break;
-        }
-        if (pass > kFixPasses) {
-            // rank = own place in the piece, and for every other piece its
-            // elements before this one (equal keys of earlier pieces are)
-            for (uint32_t slot = tid; slot < sm.sbeg[Kg]; slot += NT) {
-                uint32_t k = 0;
-                while (k + 1u < Kg && sm.sbeg[k + 1u] <= slot) ++k;
-                if (slot >= sm.send[k]) continue;
-                const uint64_t key = E[slot];
-                uint32_t rank = slot - sm.sbeg[k];
-                for (uint32_t j = 0; j < Kg; ++j) {
-                    if (j == k) continue;
-                    const uint32_t beg = sm.sbeg[j];
-                    uint32_t lo = beg, hi = sm.send[j];
-                    while (lo < hi) {
-                        const uint32_t mid = (lo + hi) >> 1;
-                        if (E[mid] < key || (E[mid] == key && j < k)) lo = mid + 1u;
-                        else hi = mid;
-                    }
-                    rank += lo - beg;
-                }
-                T[rank] = (uint16_t)slot;
-            }
+    for (bool exact = false;;) {
+        double m[EM];
+        WordRow o;
+        for (uint32_t lvl = 0;;) {
+            word_merge_level<EM, Items>(X, sm.items, lvl, sm.sent, wscr, wave, lane, m, o);
+            if (++lvl == nlev) break;
+            word_put_lds(X, o, m, lane);
             lds_barrier();
         }
+        // the words are read: the keys take their place, by slot
+        word_row_put(o, m, lane, [&](uint32_t c, double a, double z) { sm.tags[c] = word_slot(a) | word_slot(z) << 16; });
+        load_u64<U, W>(src_k + gb, glast, st, wave, lane, [](uint32_t) {}, store_lds);
+        lds_barrier();
+        if (exact || shift == 0u || sm.order.ordered(E, sm.tags, cnt, tid)) break;
+        exact = true;
+        sm.order.template second_words<(TOUT + NT - 1u) / NT>(E, sm.tags, cnt, kmin, shift, tid);
+        if (tid < Kg)   // the slots past each piece hold the sentinel again
+            for (uint32_t x = sm.send[tid]; x & 3u; ++x) X[x] = kt_sentinel();
+        lds_barrier();
     }
-    auto store = [&](uint64_t* out, uint64_t x) {
-        typedef __attribute__((address_space(1))) uint64_t gu64_t;
-        gu64_t* g = (gu64_t*)out + obase;
-        const bool vec = ((uintptr_t)(out + obase) & 15u) == 0;
-        for (uint32_t c = tid; 2u * c < cnt; c += NT) {
-            const uint32_t w = sm.tags[c];
-            if (vec && 2u * c + 1u < cnt) {
-                *reinterpret_cast<gu64x2*>(g + 2u * c) = u64x2{E[w & 0xFFFFu] ^ x, E[w >> 16] ^ x};
-            } else {
-                g[2u * c] = E[w & 0xFFFFu] ^ x;
-                if (2u * c + 1u < cnt) g[2u * c + 1u] = E[w >> 16] ^ x;
-            }
-        }
-    };
-    store(dst_k, flip_out);
+    store_by_tags<NT>(dst_k + obase, E, sm.tags, cnt, flip_out, tid);
     if constexpr (PAIRS) {   // the values in the keys' place
         lds_barrier();
         load_u64<U, W>(src_v + gb, glast, st, wave, lane, [](uint32_t) {}, store_lds);
         lds_barrier();
-        store(dst_v, 0ull);
+        store_by_tags<NT>(dst_v + obase, E, sm.tags, cnt, 0ull, tid);
     }
 }
 
