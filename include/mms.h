@@ -219,8 +219,10 @@ int mms_segmented_sort(const uint32_t* d_kin, uint32_t* d_kout, const uint32_t* 
  * keys-only sorts and MMS_PAIRS for key-value sorts; a kind with no entries
  * uses the keys-only ones.  A sort of n elements uses the first entry of its
  * kind with ceil(log2 n) <= max_log2_n, else the last one; a batched sort of
- * num_segs segments holding n elements in all uses the entry for n, with its
- * base tile capped at max(2048, n / num_segs) (shape 0 otherwise).
+ * num_segs segments holding n elements in all uses the entry for n, with the
+ * smallest base tile that sorts every segment in one pass (shapes 2, 5 and,
+ * for keys, 6), else its own one capped at max(2048, n / num_segs) (shape 2
+ * otherwise).
  *   fanout      merge fan-out K (power of two, 2..16)
  *   merge_tile  keys-only merge output tile (multiple of 256, 1024..8192;
  *               key-value merges use 4096 whatever the entry says)

@@ -145,14 +145,21 @@ Tune tune_for(uint64_t n, bool pairs) {
     return t;
 }
 
-// A batch of ns segments holding `total` elements has the parallel work of a
-// sort of `total` elements, so it takes that size's launch parameters; its
-// base tile stays within the mean segment (a larger tile would mostly sort
-// sentinels), else the 2048-key shape.
-Tune tune_for_batch(uint64_t total, uint64_t ns, bool pairs) {
+// A batch of ns segments holding `total` elements, the longest of maxn, has
+// the parallel work of a sort of `total` elements, so it takes that size's
+// launch parameters.  Its base tile is the smallest that sorts every segment in
+// one pass, if one does (a tile's waves and merge steps of sentinels are left
+// out, so the shorter segments lose little: 4096 segments of 2^6 to 2^12 keys
+// 89.9 us in 2048-key tiles and a merge round, 72.8 in 4096-key ones; pairs
+// 157.9 and 95.9; 3000 of 2^8 to 2^13 keys 105.8 and, in 8192-key ones, 84.5);
+// else it stays within the mean segment or at 2048.
+Tune tune_for_batch(uint64_t total, uint64_t ns, uint64_t maxn, bool pairs) {
     Tune t = tune_for(std::max<uint64_t>(total, 1), pairs);
     const uint64_t mean = ns ? total / ns : total;
-    if (mms::base_tile(t.base) > std::max<uint64_t>(mms::kT1, mean)) t.base = 0;
+    if (maxn <= mms::base_tile(2)) t.base = 2;
+    else if (maxn <= mms::base_tile(5)) t.base = 5;
+    else if (!pairs && maxn <= mms::base_tile(6)) t.base = 6;
+    else if (mms::base_tile(t.base) > std::max<uint64_t>(mms::kT1, mean)) t.base = 2;
     return t;
 }
 
@@ -547,7 +554,7 @@ int make_seg_plan(const uint64_t* off, uint64_t ns, uint32_t flags, SegPlan& sp)
         }
     }
     if (maxn >= (1ull << 32)) return fail(MMS_EINVAL, "a segment holds 2^32 or more elements");
-    build_batch_tasks(sp.seg_n.data(), sp.seg_n.size(), sp.pairs, tune_for_batch(sp.total, sp.seg_n.size(), sp.pairs),
+    build_batch_tasks(sp.seg_n.data(), sp.seg_n.size(), sp.pairs, tune_for_batch(sp.total, sp.seg_n.size(), maxn, sp.pairs),
                       sp.bt);
     sp.off_vals = align_up(sp.total * 4);
     sp.off_table = sp.off_vals + (sp.pairs ? align_up(sp.total * 4) : 0);

@@ -511,7 +511,7 @@ template <int W>
 static hipError_t launch_tile_net(bool pairs, const Phase& ph, const Bufs& b, uint32_t flip, hipStream_t s) {
     const dim3 grid((unsigned)ph.tiles), block(W * 64);
     if (pairs) {
-        if constexpr (W == 4) hipLaunchKernelGGL((k_tile_net_pairs<W>), grid, block, 0, s, ph, b, flip);
+        if constexpr (W <= 4) hipLaunchKernelGGL((k_tile_net_pairs<W>), grid, block, 0, s, ph, b, flip);
         else return hipErrorInvalidValue;
     } else {
         hipLaunchKernelGGL((k_tile_net_keys<W>), grid, block, 0, s, ph, b, flip);
@@ -522,10 +522,10 @@ static hipError_t launch_tile_net(bool pairs, const Phase& ph, const Bufs& b, ui
 hipError_t launch_tile_sort(bool pairs, const Phase& ph, const Bufs& b, uint32_t flip, int base_shape,
                             hipStream_t s) {
     if (ph.tiles == 0) return hipSuccess;
+    if (base_shape == 2) return launch_tile_net<base_w(2)>(pairs, ph, b, flip, s);
     if (base_shape == 5) return launch_tile_net<base_w(5)>(pairs, ph, b, flip, s);
     if (!pairs) {
         if (base_shape == 1) return launch_tile_sort_keys<base_e(1), base_w(1)>(ph, b, flip, s);
-        if (base_shape == 2) return launch_tile_net<base_w(2)>(false, ph, b, flip, s);
         if (base_shape == 3) return launch_tile_sort_keys<base_e(3), base_w(3)>(ph, b, flip, s);
         if (base_shape == 4) return launch_tile_sort_keys<base_e(4), base_w(4)>(ph, b, flip, s);
         if (base_shape == 6) return launch_tile_net<base_w(6)>(false, ph, b, flip, s);

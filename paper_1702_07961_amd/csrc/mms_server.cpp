@@ -290,15 +290,16 @@ Batch form_batch(mms_server* s, int stream, int slot) {
     const Req& head = s->reqs[s->admitted.front()];
     const uint32_t kind = head.r.flags;
     const uint32_t cls = size_class(head.r.n);
-    uint64_t cand_keys = 0, cand_n = 0;
+    uint64_t cand_keys = 0, cand_n = 0, cand_max = 0;
     for (uint64_t t : s->admitted) {
         const Req& q = s->reqs[t];
         if (q.r.flags != kind || size_class(q.r.n) != cls || cand_n >= s->cfg.max_batch_requests) continue;
         if (cand_n && cand_keys + q.r.n > s->cfg.max_batch_keys) continue;
         cand_keys += q.r.n;
+        cand_max = std::max<uint64_t>(cand_max, q.r.n);
         ++cand_n;
     }
-    b.tune = tune_for_batch(cand_keys, cand_n, (kind & MMS_PAIRS) != 0);
+    b.tune = tune_for_batch(cand_keys, cand_n, cand_max, (kind & MMS_PAIRS) != 0);
     uint64_t keys = 0, ntasks = 0;
     std::vector<uint64_t> phases, mine;
     std::deque<uint64_t> rest;
