@@ -163,15 +163,6 @@ Tune tune_for_batch(uint64_t total, uint64_t ns, uint64_t maxn, bool pairs) {
     return t;
 }
 
-// One resident workgroup per compute unit for the persistent merge kernel.
-unsigned persistent_grid() {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 256;
-    int cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 256;
-    return (unsigned)cus;
-}
-
 // ---- the phase loop ----------------------------------------------------------
 namespace {
 struct PhaseList {
@@ -200,7 +191,7 @@ int run_phases(bool pairs, const PhaseList& pl, const Bufs& b, uint32_t* table, 
         {
             Timed tm(MMS_KERNEL_MERGE, s);
             if (pairs) e = launch_merge_pairs(ph, b, ra, table, flip, s);
-            else e = launch_merge_keys(ph, b, ra, table, flip, persistent_grid(), tune.variant, s);
+            else e = launch_merge_keys(ph, b, ra, table, flip, tune.variant, s);
         }
         if (e != hipSuccess) return hip_fail(e, "merge launch");
     }

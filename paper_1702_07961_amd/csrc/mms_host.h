@@ -57,9 +57,6 @@ inline uint32_t rounds_for(uint64_t n, uint32_t T, uint32_t K) {
     return r;
 }
 
-// Workgroups of the persistent merge kernel (one per compute unit).
-unsigned persistent_grid();
-
 // The tile tasks of a batch of non-empty segments: phases[0] is the base
 // case, phases[1 + r] merge round r.  Every segment is planned exactly as a
 // plain sort of its own length with the batch's tuning; segment s with R_s

@@ -155,12 +155,12 @@ hipError_t launch_corank_queries(const uint32_t* keys, uint64_t n, uint64_t L, u
 hipError_t launch_merge_pairs(const Phase& ph, const Bufs& b, const RoundArgs& ra, const uint32_t* table,
                               uint32_t flip, hipStream_t s);
 
-// Keys-only merge round, persistent: `grid` compute units' worth of
-// workgroups walk the phase's tiles.  variant 0 and 3: 8 waves, 256-key row
-// blocks; 1: 16 waves, 256-key row blocks; 2: 8 waves, 128-key row blocks for
-// merge tiles up to 4096 (256-key ones above); 4: the minBlockHeap merge.
+// Keys-only merge round (one workgroup per tile).  variant 0 and 3: 8 waves,
+// 256-key row blocks (16 waves for tiles past 7680); 1: 16 waves, 128-key row
+// blocks up to 7424-key tiles (256-key ones above); 2: 8 waves, 128-key row
+// blocks up to 3584-key tiles (as 0 above); 4: the minBlockHeap merge.
 hipError_t launch_merge_keys(const Phase& ph, const Bufs& b, const RoundArgs& ra, const uint32_t* table,
-                             uint32_t flip, unsigned grid, int variant, hipStream_t s);
+                             uint32_t flip, int variant, hipStream_t s);
 
 // Keys-only merge round with a minBlockHeap of 64-key nodes per wave (merge
 // shape 4): one wave per output tile.

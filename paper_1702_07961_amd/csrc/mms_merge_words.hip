@@ -21,6 +21,7 @@
 #include "mms_device64.h"
 #include "mms_device_kt.h"
 #include "mms_internal.h"
+#include "mms_load_steps.h"
 #include "mms_order64.h"
 #include "mms_tile_plan.h"
 #include "mms_word_merge.h"
@@ -35,29 +36,6 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x2a4 __attribute__((ext_vector_type(2), aligned(4)));
 typedef const __attribute__((address_space(1))) u32x2a4 cgu32x2a4;
 typedef __attribute__((address_space(1))) u32x2 gu32x2;
-
-// Pieces are loaded in steps of 128 elements, two per lane.  Step e of the
-// tile sits in lane e of every wave: where its elements come from (in the
-// group), its first LDS slot and its length.
-struct LoadSteps {
-    uint32_t src, dst, cnt, total;
-};
-__device__ __forceinline__ LoadSteps load_steps(const PieceLayout& pc, uint32_t s, uint32_t Kg, uint64_t L, int lane) {
-    const uint32_t own = (pc.len + 127u) >> 7;   // lanes k < Kg hold piece k, the others none
-    const uint32_t before = excl_scan16(own);
-    uint32_t k = 0;
-    for (uint32_t j = 0; j + 1u < Kg; ++j)   // pieces whose steps end at or before this lane's
-        k += (uint32_t)__builtin_amdgcn_readlane((int)(before + own), (int)j) <= (uint32_t)lane ? 1u : 0u;
-    const uint32_t from = (uint32_t)((uint64_t)(uint32_t)lane * L) + s;   // lane k: piece k's first element
-    auto of = [&](uint32_t x) { return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(k << 2), (int)x); };
-    const uint32_t at = ((uint32_t)lane - of(before)) << 7;
-    LoadSteps r;
-    r.src = of(from) + at;
-    r.dst = of(pc.sb) + at;
-    r.cnt = min(of(pc.len) - at, 128u);   // meaningful below total only
-    r.total = (uint32_t)__builtin_amdgcn_readlane((int)(before + own), (int)(Kg - 1u));
-    return r;
-}
 
 }  // namespace
 
@@ -123,7 +101,7 @@ __global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge_pairs(Phase 
         e = (obeg + Tout >= glen) ? nk : min(max(table[(t + 1) * K + k], s), nk);
     }
     const PieceLayout pc = piece_layout(s, e, Kg, cnt, lane);
-    const LoadSteps st = load_steps(pc, s, Kg, L, lane);
+    const LoadSteps st = load_steps<7>(pc, s, Kg, L, lane);
     cgu32* gk = gptr(tr.src_k) + gb;
     const uint32_t glast = (uint32_t)glen - 2u;   // a group of two runs or more holds more than a base tile
     constexpr uint32_t U = 32 / W;                   // steps a wave has in flight
@@ -315,7 +293,7 @@ __global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge64(Phase64 ph
         e = (obeg + Tout >= glen) ? nk : min(max(table[(t + 1) * K + k], s), nk);
     }
     const PieceLayout pc = piece_layout(s, e, Kg, cnt, lane);
-    const LoadSteps st = load_steps(pc, s, Kg, L, lane);
+    const LoadSteps st = load_steps<7>(pc, s, Kg, L, lane);
     uint64_t kmin = ~0ull, kmax = 0;
     if (pc.len) {   // lanes of non-empty pieces
         cgu64* p = gptr64(src_k) + (gb + (uint64_t)(uint32_t)lane * L + s);

@@ -112,60 +112,68 @@ __device__ __forceinline__ void row_sort(uint32_t (&m)[EM], uint32_t* scr, int l
 }
 
 // ---- items --------------------------------------------------------------------
-// Item words, all in chunks: word 0 = first chunk of the pair's run A (bits
-// 0..11) and of run B (12..23); word 1 = end of run B (0..11), first output
-// of the item inside the pair (12..23), outputs (24..31, 0: no item).
-constexpr uint32_t kItemsPerLevel = 64;
-constexpr uint32_t kItemLevels = 4;
-constexpr uint32_t kItemWords = kItemLevels * kItemsPerLevel * 2u + kItemLevels;   // items, then the item counts
-
-// Outputs of one item at most: a block's 16*EM less two chunks, which the
-// block may spend on outputs of the item before it.
+// Outputs of one item at most, in chunks: a block's 16*EM keys less two chunks,
+// which the block may spend on outputs of the item before it.
 template <int EM> constexpr uint32_t kItemChunks = 4u * EM - 2u;
 
-// The items of every level of a tile (one wave).  Lane q < 15 takes pair p of
-// level l (8, 4, 2 and 1 pairs): its runs' bounds from the piece starts, the
-// fewest items that hold it, and equal shares; the items of one pair are then
-// written by as many lanes.  sbeg: first slots of the pieces, sbeg[Kg] the end.
-template <int EM>
-__device__ __forceinline__ void build_items(uint32_t* items, const uint32_t* sbeg, uint32_t Kg, int lane) {
-    const uint32_t q = (uint32_t)lane;
-    const uint32_t l = q < 8u ? 0u : q < 12u ? 1u : q < 14u ? 2u : 3u;
-    const uint32_t p = q < 8u ? q : q < 12u ? q - 8u : q < 14u ? q - 12u : 0u;
-    const uint32_t a = sbeg[min((2u * p) << l, Kg)] >> 2;
-    const uint32_t b = sbeg[min((2u * p + 1u) << l, Kg)] >> 2;
-    const uint32_t e = sbeg[min((2u * p + 2u) << l, Kg)] >> 2;
-    const uint32_t size = q < 15u ? e - a : 0u;
-    const uint32_t nit = udiv_small(size + kItemChunks<EM> - 1u, kItemChunks<EM>);
-    const uint32_t share = nit ? udiv_small(size + nit - 1u, nit) : 0u;
-    // first item of the pair in its level: items of the level's pairs before it
-    const uint32_t before = excl_scan16(nit);
-    const uint32_t lv0 = l == 0u ? 0u : l == 1u ? 8u : l == 2u ? 12u : 14u;
-    const uint32_t first = before - (uint32_t)__builtin_amdgcn_ds_bpermute((int)(lv0 << 2), (int)before);
-    const uint32_t w0 = a | (b << 12);
+// Item words, all in chunks: word 0 = first chunk of the pair's run A (bits
+// 0..11) and of run B (12..23); word 1 = end of run B (0..11), first output
+// of the item inside the pair (12..23), outputs (24..31, 0: no item).  After
+// the items, for each pair (8, 4, 2 and 1), the items of its level up to its
+// end.
+template <int EM, int W, uint32_t TMAX>
+struct RowItems {
+    static constexpr uint32_t kChunks = TMAX / 4u + kMaxFanout;   // LDS slots of a tile
+    static constexpr uint32_t kRows = 4u * W;
+    // a pair's last item may be partial
+    static constexpr uint32_t kPerLevel = kChunks / kItemChunks<EM> + kMaxFanout / 2u;
+    static constexpr uint32_t kWords = 4u * kPerLevel * 2u + 16u;
+    static_assert(kChunks < 4096u, "chunk numbers take 12 bits");
+    static_assert((kChunks + kItemChunks<EM> - 1u) / kItemChunks<EM> <= kRows, "a pass holds any pair");
+
+    // The items of every level of a tile (one wave).  Lane q < 15 takes pair p
+    // of level l (8, 4, 2 and 1 pairs): its runs' bounds from the piece starts,
+    // the fewest items that hold it, and equal shares; the items of one pair
+    // are then written by as many lanes.  sbeg: first slots of the pieces,
+    // sbeg[Kg] the end.
+    __device__ static __forceinline__ void build(uint32_t* items, const uint32_t* sbeg, uint32_t Kg, int lane) {
+        const uint32_t q = (uint32_t)lane;
+        const uint32_t l = q < 8u ? 0u : q < 12u ? 1u : q < 14u ? 2u : 3u;
+        const uint32_t p = q < 8u ? q : q < 12u ? q - 8u : q < 14u ? q - 12u : 0u;
+        const uint32_t a = sbeg[min((2u * p) << l, Kg)] >> 2;
+        const uint32_t b = sbeg[min((2u * p + 1u) << l, Kg)] >> 2;
+        const uint32_t e = sbeg[min((2u * p + 2u) << l, Kg)] >> 2;
+        const uint32_t size = q < 15u ? e - a : 0u;
+        const uint32_t nit = udiv_small(size + kItemChunks<EM> - 1u, kItemChunks<EM>);
+        const uint32_t share = nit ? udiv_small(size + nit - 1u, nit) : 0u;
+        // first item of the pair in its level: items of the level's pairs before it
+        const uint32_t before = excl_scan16(nit);
+        const uint32_t lv0 = l == 0u ? 0u : l == 1u ? 8u : l == 2u ? 12u : 14u;
+        const uint32_t first = before - (uint32_t)__builtin_amdgcn_ds_bpermute((int)(lv0 << 2), (int)before);
+        const uint32_t w0 = a | (b << 12);
 #pragma unroll 1
-    for (uint32_t s = 0; s < 15u; ++s) {
-        const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)nit, (int)s);
-        const uint32_t f = (uint32_t)__builtin_amdgcn_readlane((int)first, (int)s);
-        const uint32_t sh = (uint32_t)__builtin_amdgcn_readlane((int)share, (int)s);
-        const uint32_t sz = (uint32_t)__builtin_amdgcn_readlane((int)size, (int)s);
-        const uint32_t ww = (uint32_t)__builtin_amdgcn_readlane((int)w0, (int)s);
-        const uint32_t en = (uint32_t)__builtin_amdgcn_readlane((int)e, (int)s);
-        const uint32_t lv = s < 8u ? 0u : s < 12u ? 1u : s < 14u ? 2u : 3u;
-        if (q < n) {
-            const uint32_t d0 = q * sh;
-            const uint32_t cnt = sz > d0 ? min(sh, sz - d0) : 0u;
-            uint32_t* it = items + 2u * (lv * kItemsPerLevel + f + q);
-            *reinterpret_cast<uint2*>(it) = make_uint2(ww, en | (d0 << 12) | (cnt << 24));
+        for (uint32_t s = 0; s < 15u; ++s) {
+            const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)nit, (int)s);
+            const uint32_t f = (uint32_t)__builtin_amdgcn_readlane((int)first, (int)s);
+            const uint32_t sh = (uint32_t)__builtin_amdgcn_readlane((int)share, (int)s);
+            const uint32_t sz = (uint32_t)__builtin_amdgcn_readlane((int)size, (int)s);
+            const uint32_t ww = (uint32_t)__builtin_amdgcn_readlane((int)w0, (int)s);
+            const uint32_t en = (uint32_t)__builtin_amdgcn_readlane((int)e, (int)s);
+            const uint32_t lv = s < 8u ? 0u : s < 12u ? 1u : s < 14u ? 2u : 3u;
+            for (uint32_t j = q; j < n; j += 64u) {
+                const uint32_t d0 = j * sh;
+                const uint32_t cnt = sz > d0 ? min(sh, sz - d0) : 0u;
+                uint32_t* it = items + 2u * (lv * kPerLevel + f + j);
+                *reinterpret_cast<uint2*>(it) = make_uint2(ww, en | (d0 << 12) | (cnt << 24));
+            }
         }
+        if (q < 15u) items[8u * kPerLevel + q] = first + nit;
     }
-    const uint32_t tot = first + nit;   // of the level, in its last pair's lane
-    if (q == 7u || q == 11u || q == 13u || q == 14u) items[kItemLevels * kItemsPerLevel * 2u + l] = tot;
-}
+};
 
 // ---- one item -------------------------------------------------------------------
 struct RowOut {
-    uint32_t chunk;   // first output chunk of the item, counted from its pair's first slot
+    uint32_t chunk;   // first output chunk of the item (of the tile's slots)
     uint32_t pad;     // leading chunks of the block that belong to the item before (0 to 2)
     uint32_t cnt;     // chunks of the item (0: none)
 };
@@ -193,9 +201,9 @@ __device__ __forceinline__ RowOut row_merge(const uint32_t* X, uint2 w, const ui
     const uint32_t la = aB - aA, lb = en - aB;
     uint32_t lo = d0 > lb ? d0 - lb : 0u;
     uint32_t hi = min(d0, la);
-    // A lane past the range probes up to 16 chunks past it (inside the
-    // workgroup's LDS: the layouts keep that much before and after the level
-    // buffers) and does not count; at most 15 probes precede the split.
+    // A lane past the range probes up to 31 chunks past it (inside the
+    // workgroup's LDS: the layout keeps that much before and after the keys)
+    // and does not count; at most 15 probes precede the split.
     const uint32_t* pA = X + (4u * aA + row);
     const uint32_t* pB = X + (4u * (aB + d0) - 1u - row);
     while (__ballot(lo < hi)) {
@@ -242,29 +250,52 @@ __device__ __forceinline__ RowOut row_merge(const uint32_t* X, uint2 w, const ui
 #pragma unroll
     for (int e = 0; e < EM; ++e) m[e] = min(a[e], b[e]);
     row_sort<EM>(m, scr, lane);
-    return RowOut{d0, pad, w.y >> 24};
+    return RowOut{aA + d0, pad, w.y >> 24};
 }
 
-// One merge level: the workgroup's rows take the level's items in turn.
-template <int EM, int W, class Put>
-__device__ __forceinline__ void merge_level_rows(const uint32_t* X, const uint32_t* items, uint32_t lvl,
-                                                 const uint32_t* sent, uint32_t* scr, int wave, int lane,
-                                                 const Put& put) {
-    constexpr uint32_t ROWS = 4u * W;
-    const uint32_t total =
-        (uint32_t)__builtin_amdgcn_readfirstlane((int)items[kItemLevels * kItemsPerLevel * 2u + lvl]);
-    for (uint32_t base = 4u * (uint32_t)wave; base < total; base += ROWS) {
-        const uint32_t at = base + ((uint32_t)lane >> 4);
-        uint2 w = *reinterpret_cast<const uint2*>(items + 2u * (lvl * kItemsPerLevel + at));
-        if (at >= total) w = make_uint2(0u, 0u);
-        uint32_t m[EM];
-        const RowOut o = row_merge<EM>(X, w, sent, scr, m, lane);
-        const uint32_t t0 = row_chunk0<EM>((uint32_t)lane & 15u) - o.pad;   // wraps for the chunk not stored
-        const uint32_t at0 = (w.x & 0xFFFu) + o.chunk + t0;
+// The outputs of a sorted item: put(chunk, its four keys).
+template <int EM, class Put>
+__device__ __forceinline__ void row_put(const RowOut& o, const uint32_t (&m)[EM], int lane, const Put& put) {
+    const uint32_t t0 = row_chunk0<EM>((uint32_t)lane & 15u) - o.pad;   // wraps for the chunks not stored
 #pragma unroll
-        for (int c = 0; c < EM / 4; ++c)
-            if (t0 + kRowChunkStep<EM> * (uint32_t)c < o.cnt)
-                put(at0 + kRowChunkStep<EM> * (uint32_t)c, m[4 * c], m[4 * c + 1], m[4 * c + 2], m[4 * c + 3]);
+    for (int c = 0; c < EM / 4; ++c) {
+        const uint32_t t = t0 + kRowChunkStep<EM> * (uint32_t)c;
+        if (t < o.cnt) put(o.chunk + t, m[4 * c], m[4 * c + 1], m[4 * c + 2], m[4 * c + 3]);
+    }
+}
+template <int EM>
+__device__ __forceinline__ void row_put_lds(uint32_t* X, const RowOut& o, const uint32_t (&m)[EM], int lane) {
+    row_put(o, m, lane, [&](uint32_t c, uint32_t k0, uint32_t k1, uint32_t k2, uint32_t k3) {
+        *reinterpret_cast<uint4*>(X + 4u * c) = make_uint4(k0, k1, k2, k3);
+    });
+}
+
+// One merge level in place: the rows of a pass read and sort one item each,
+// the workgroup meets, and the items go back to their pairs' slots.  A pass
+// takes as many whole pairs as it has rows for (nearly always all), so it
+// writes no slot that a later one reads.  The level's last pass leaves its
+// items in m and o (o.cnt = 0: none) instead, after the meeting.
+template <int EM, class Items>
+__device__ __forceinline__ void row_merge_level(uint32_t* X, const uint32_t* items, uint32_t lvl, const uint32_t* sent,
+                                                uint32_t* scr, int wave, int lane, uint32_t (&m)[EM], RowOut& o) {
+    const uint32_t pairs = 8u >> lvl;
+    const uint32_t upto = items[8u * Items::kPerLevel + min(16u - 2u * pairs + (uint32_t)lane, 14u)];
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)upto, (int)(pairs - 1u));
+    for (uint32_t beg = 0;;) {
+        const uint64_t fit = __ballot((uint32_t)lane < pairs && upto <= beg + Items::kRows);
+        const uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)upto, __popcll(fit) - 1);
+        const uint32_t at = beg + 4u * (uint32_t)wave;   // the wave's first item
+        o = RowOut{0, 0, 0};
+        if (at < end) {
+            const uint32_t it = at + ((uint32_t)lane >> 4);
+            uint2 w = *reinterpret_cast<const uint2*>(items + 2u * (lvl * Items::kPerLevel + it));
+            if (it >= end) w = make_uint2(0u, 0u);
+            o = row_merge<EM>(X, w, sent, scr, m, lane);
+        }
+        lds_barrier();   // the pass's reads are done
+        if (end >= total) break;
+        row_put_lds(X, o, m, lane);
+        beg = end;
     }
 }
 
