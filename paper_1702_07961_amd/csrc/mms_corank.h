@@ -138,12 +138,25 @@ __device__ uint32_t corank_rounds(const KeyT* __restrict__ keys, uint64_t gb, ui
                 for (uint32_t e = 0; e < 8; ++e) rank += sh->comp[m + e] < comp ? 1u : 0u;
             }
         } else {
+            // c precedes this lane's key if c < key, or c <= key for the lanes
+            // after its own: the borrow of c - key - [lane > m], which a third
+            // instruction adds to the rank
+            const uint32_t klo = (uint32_t)comp, khi = (uint32_t)(comp >> 32);
+            uint64_t after = ~1ull;   // lanes after candidate m's
 #pragma unroll 2
             for (uint32_t m = 0; m < total; m += 8) {
 #pragma unroll
                 for (uint32_t e = 0; e < 8; ++e) {
                     const uint64_t c = sh->comp[m + e];
-                    rank += (c < comp || (c == comp && m + e < (uint32_t)lane)) ? 1u : 0u;
+                    uint32_t t;
+                    asm("s_mov_b64 vcc, %4\n\t"
+                        "v_subb_co_u32 %1, vcc, %2, %5, vcc\n\t"
+                        "v_subb_co_u32 %1, vcc, %3, %6, vcc\n\t"
+                        "v_addc_co_u32 %0, vcc, 0, %0, vcc"
+                        : "+v"(rank), "=&v"(t)
+                        : "v"((uint32_t)c), "v"((uint32_t)(c >> 32)), "s"(after), "v"(klo), "v"(khi)
+                        : "vcc");
+                    after <<= 1;
                 }
             }
         }
