@@ -169,8 +169,8 @@ __global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge_pairs(Phase 
     gu32* ok = gptr(tr.dst_k) + obase;
     gu32* ov = gptr(tr.dst_v) + obase;
     const bool vec = (((uintptr_t)(tr.dst_k + obase) | (uintptr_t)(tr.dst_v + obase)) & 7u) == 0;
-    word_row_put(o, m, lane, [&](uint32_t c, double a, double z) {
-        const uint32_t at = 2u * c;
+    word_row_put(o, m, lane, [&](int c, int step, double a, double z) {
+        const uint32_t at = 2u * (uint32_t)(c + step);
         if (vec && at + 2u <= cnt) {
             *reinterpret_cast<gu32x2*>(ok + at) = u32x2{kt_key(a) ^ flip_out, kt_key(z) ^ flip_out};
             *reinterpret_cast<gu32x2*>(ov + at) = u32x2{V[kt_tag(a)], V[kt_tag(z)]};
@@ -351,7 +351,9 @@ __global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge64(Phase64 ph
             lds_barrier();
         }
         // the words are read: the keys take their place, by slot
-        word_row_put(o, m, lane, [&](uint32_t c, double a, double z) { sm.tags[c] = word_slot(a) | word_slot(z) << 16; });
+        word_row_put(o, m, lane, [&](int c, int step, double a, double z) {
+            (sm.tags + c)[step] = word_slot(a) | word_slot(z) << 16;
+        });
         load_u64<U, W>(src_k + gb, glast, st, wave, lane, [](uint32_t) {}, store_lds);
         lds_barrier();
         if (exact || shift == 0u || sm.order.ordered(E, sm.tags, cnt, tid)) break;

@@ -238,13 +238,14 @@ __device__ __forceinline__ RowOut row_merge(const uint32_t* X, uint2 w, const ui
             get(b, c, Bp + 64u * (Q - 1u - (uint32_t)c), true);
         }
     } else {
-        // chunks past a run's end read the largest key
-        const uint32_t ra = la - p, rb = lb - q;
+        // chunks past a run's end read the largest key; its address takes each
+        // read's offset off, so the offsets stay in the instructions
+        const int ra = (int)(la - p - i), rb = (int)(lb - q) - (int)(15u - i);   // chunks from the lane's first on
 #pragma unroll
         for (int c = 0; c < (int)Q; ++c) {
-            get(a, c, i + 16u * (uint32_t)c < ra ? Ap + 64u * (uint32_t)c : sent, false);
-            const uint32_t cb = Q - 1u - (uint32_t)c;
-            get(b, c, 15u - i + 16u * cb < rb ? Bp + 64u * cb : sent, true);
+            get(a, c, (16 * c < ra ? Ap : sent - 64 * c) + 64 * c, false);
+            const int cb = (int)Q - 1 - c;
+            get(b, c, (16 * cb < rb ? Bp : sent - 64 * cb) + 64 * cb, true);
         }
     }
 #pragma unroll
@@ -253,20 +254,21 @@ __device__ __forceinline__ RowOut row_merge(const uint32_t* X, uint2 w, const ui
     return RowOut{aA + d0, pad, w.y >> 24};
 }
 
-// The outputs of a sorted item: put(chunk, its four keys).
+// The outputs of a sorted item: put(the lane's first chunk, a step from it that
+// is a constant, four keys).
 template <int EM, class Put>
 __device__ __forceinline__ void row_put(const RowOut& o, const uint32_t (&m)[EM], int lane, const Put& put) {
     const uint32_t t0 = row_chunk0<EM>((uint32_t)lane & 15u) - o.pad;   // wraps for the chunks not stored
 #pragma unroll
     for (int c = 0; c < EM / 4; ++c) {
-        const uint32_t t = t0 + kRowChunkStep<EM> * (uint32_t)c;
-        if (t < o.cnt) put(o.chunk + t, m[4 * c], m[4 * c + 1], m[4 * c + 2], m[4 * c + 3]);
+        const uint32_t step = kRowChunkStep<EM> * (uint32_t)c;
+        if (t0 + step < o.cnt) put((int)(o.chunk + t0), (int)step, m[4 * c], m[4 * c + 1], m[4 * c + 2], m[4 * c + 3]);
     }
 }
 template <int EM>
 __device__ __forceinline__ void row_put_lds(uint32_t* X, const RowOut& o, const uint32_t (&m)[EM], int lane) {
-    row_put(o, m, lane, [&](uint32_t c, uint32_t k0, uint32_t k1, uint32_t k2, uint32_t k3) {
-        *reinterpret_cast<uint4*>(X + 4u * c) = make_uint4(k0, k1, k2, k3);
+    row_put(o, m, lane, [&](int c, int step, uint32_t k0, uint32_t k1, uint32_t k2, uint32_t k3) {
+        *reinterpret_cast<uint4*>(X + 4 * c + 4 * step) = make_uint4(k0, k1, k2, k3);
     });
 }
 

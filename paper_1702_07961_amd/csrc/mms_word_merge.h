@@ -238,13 +238,16 @@ __device__ __forceinline__ WordRow word_row_merge(const double* X, uint2 w, cons
             m[2 * c + 1] = kt_min(a.y, b.x);
         }
     } else {
-        // chunks past a run's end read the sentinel
-        const uint32_t ra = la - p, rb = lb - q;
+        // chunks past a run's end read the sentinel; its address takes each
+        // read's offset off, so the offsets stay in the instructions
+        const int ra = (int)(la - p - i), rb = (int)(lb - q) - (int)(15u - i);   // chunks from the lane's first on
 #pragma unroll
-        for (uint32_t c = 0; c < Q; ++c) {
-            const uint32_t cb = Q - 1u - c;
-            const d2 a = *reinterpret_cast<const d2*>(i + 16u * c < ra ? Ap + 32u * c : sent);
-            const d2 b = *reinterpret_cast<const d2*>(15u - i + 16u * cb < rb ? Bp + 32u * cb : sent);
+        for (int c = 0; c < (int)Q; ++c) {
+            const int cb = (int)Q - 1 - c;
+            const double* from_a = 16 * c < ra ? Ap : sent - 32 * c;
+            const double* from_b = 16 * cb < rb ? Bp : sent - 32 * cb;
+            const d2 a = *reinterpret_cast<const d2*>(from_a + 32 * c);
+            const d2 b = *reinterpret_cast<const d2*>(from_b + 32 * cb);
             m[2 * c] = kt_min(a.x, b.y);
             m[2 * c + 1] = kt_min(a.y, b.x);
         }
@@ -253,21 +256,23 @@ __device__ __forceinline__ WordRow word_row_merge(const double* X, uint2 w, cons
     return WordRow{aA + d0, d0 - p - q, w.y >> 24};
 }
 
-// The outputs of a sorted item: put(chunk, word, word).
+// The outputs of a sorted item: put(the lane's first chunk, a step from it that
+// is a constant, word, word).
 template <int EM, class Put>
 __device__ __forceinline__ void word_row_put(const WordRow& o, const double (&m)[EM], int lane, const Put& put) {
     const uint32_t t0 = word_chunk0<EM>((uint32_t)lane & 15u) - o.pad;   // wraps for the chunks not stored
 #pragma unroll
     for (int e = 0; e < EM; e += 2) {
         const uint32_t step = word_step<EM>((uint32_t)e);
-        if (t0 + step < o.cnt) put(o.chunk + t0 + step, m[e], m[e + 1]);
+        if (t0 + step < o.cnt) put((int)(o.chunk + t0), (int)step, m[e], m[e + 1]);
     }
 }
-
 template <int EM>
 __device__ __forceinline__ void word_put_lds(double* X, const WordRow& o, const double (&m)[EM], int lane) {
     typedef double d2 __attribute__((ext_vector_type(2)));
-    word_row_put(o, m, lane, [&](uint32_t c, double a, double z) { *reinterpret_cast<d2*>(X + 2u * c) = d2{a, z}; });
+    word_row_put(o, m, lane, [&](int c, int step, double a, double z) {
+        *reinterpret_cast<d2*>(X + 2 * c + 2 * step) = d2{a, z};
+    });
 }
 
 // One merge level in place: the rows of a pass read and sort one item each,
