@@ -102,6 +102,7 @@ __global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge_pairs(Phase 
     }
     const PieceLayout pc = piece_layout(s, e, Kg, cnt, lane);
     const LoadSteps st = load_steps<7>(pc, s, Kg, L, lane);
+    static_assert(TOUT / 128u + kMaxFanout <= 64u, "a step per lane");
     cgu32* gk = gptr(tr.src_k) + gb;
     const uint32_t glast = (uint32_t)glen - 2u;   // a group of two runs or more holds more than a base tile
     constexpr uint32_t U = 32 / W;                   // steps a wave has in flight
@@ -294,6 +295,7 @@ __global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge64(Phase64 ph
     }
     const PieceLayout pc = piece_layout(s, e, Kg, cnt, lane);
     const LoadSteps st = load_steps<7>(pc, s, Kg, L, lane);
+    static_assert(TOUT / 128u + kMaxFanout <= 64u, "a step per lane");
     uint64_t kmin = ~0ull, kmax = 0;
     if (pc.len) {   // lanes of non-empty pieces
         cgu64* p = gptr64(src_k) + (gb + (uint64_t)(uint32_t)lane * L + s);
