@@ -30,7 +30,11 @@ typedef const __attribute__((address_space(1))) uint32_t cgu32;
 typedef uint32_t u32x4a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef const __attribute__((address_space(1))) u32x4a4 cgu32x4a4;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(1))) u32x4 gu32x4;
+// four or two keys stored at a 4-byte aligned address (a batch's segments start
+// anywhere): one instruction, like the loads above
+typedef __attribute__((address_space(1))) u32x4a4 gu32x4a4;
+typedef uint32_t u32x2a4 __attribute__((ext_vector_type(2), aligned(4)));
+typedef __attribute__((address_space(1))) u32x2a4 gu32x2a4;
 
 __device__ __forceinline__ gu32* gptr(uint32_t* p) { return (gu32*)p; }
 __device__ __forceinline__ cgu32* gptr(const uint32_t* p) { return (cgu32*)p; }

@@ -128,13 +128,12 @@ __global__ __launch_bounds__(W * 64) void k_tile_sort_keys(Phase ph, Bufs b, uin
     }
 
     // wave w, lane l holds tile positions w*CH + l*E .. + E-1
-    const bool vec = ((uintptr_t)out_k & 15u) == 0;
     gu32* g = gptr(out_k);
 #pragma unroll
     for (uint32_t c = 0; c < Q; ++c) {
         const uint32_t pos = (uint32_t)wave * CH + ul * (uint32_t)E + 4u * c;
-        if (vec && pos + 4u <= cnt) {
-            *reinterpret_cast<gu32x4*>(g + pos) = u32x4{r[4 * c].k ^ flip_out, r[4 * c + 1].k ^ flip_out,
+        if (pos + 4u <= cnt) {
+            *reinterpret_cast<gu32x4a4*>(g + pos) = u32x4{r[4 * c].k ^ flip_out, r[4 * c + 1].k ^ flip_out,
                                                         r[4 * c + 2].k ^ flip_out, r[4 * c + 3].k ^ flip_out};
         } else {
 #pragma unroll
@@ -245,17 +244,16 @@ __global__ __launch_bounds__(W * 64) void k_tile_sort_pairs(Phase ph, Bufs b, ui
     }
 
     // wave w, lane l holds tile positions w*CH + l*E .. + E-1; values by tag
-    const bool vec = (((uintptr_t)out_k | (uintptr_t)out_v) & 15u) == 0;
     gu32* gk = gptr(out_k);
     gu32* gv = gptr(out_v);
 #pragma unroll
     for (uint32_t c = 0; c < Q; ++c) {
         const uint32_t pos = (uint32_t)wave * CH + ul * (uint32_t)E + 4u * c;
         const ElemKT* q = r + 4 * c;
-        if (vec && pos + 4u <= cnt) {
-            *reinterpret_cast<gu32x4*>(gk + pos) = u32x4{kt_key(q[0].d) ^ flip_out, kt_key(q[1].d) ^ flip_out,
+        if (pos + 4u <= cnt) {
+            *reinterpret_cast<gu32x4a4*>(gk + pos) = u32x4{kt_key(q[0].d) ^ flip_out, kt_key(q[1].d) ^ flip_out,
                                                          kt_key(q[2].d) ^ flip_out, kt_key(q[3].d) ^ flip_out};
-            *reinterpret_cast<gu32x4*>(gv + pos) =
+            *reinterpret_cast<gu32x4a4*>(gv + pos) =
                 u32x4{V[kt_tag(q[0].d)], V[kt_tag(q[1].d)], V[kt_tag(q[2].d)], V[kt_tag(q[3].d)]};
         } else {
 #pragma unroll
@@ -308,13 +306,12 @@ __global__ __launch_bounds__(W * 64, 8) void k_tile_net_keys(Phase ph, Bufs b, u
     }
     net_sort<NetKey, W>(X, m, cnt, lane, wave);
     net_to_memory_order(X, m, ul, (uint32_t)wave);
-    const bool vec = ((uintptr_t)out_k & 15u) == 0;
     gu32* g = gptr(out_k);
 #pragma unroll
     for (uint32_t c = 0; c < 4u; ++c) {
         const uint32_t pos = at + c * 256u;
-        if (vec && pos + 4u <= cnt) {
-            *reinterpret_cast<gu32x4*>(g + pos) = u32x4{m[4 * c] ^ flip_out, m[4 * c + 1] ^ flip_out,
+        if (pos + 4u <= cnt) {
+            *reinterpret_cast<gu32x4a4*>(g + pos) = u32x4{m[4 * c] ^ flip_out, m[4 * c + 1] ^ flip_out,
                                                         m[4 * c + 2] ^ flip_out, m[4 * c + 3] ^ flip_out};
         } else {
 #pragma unroll
@@ -368,17 +365,16 @@ __global__ __launch_bounds__(W * 64, 4) void k_tile_net_pairs(Phase ph, Bufs b, 
 #pragma unroll
     for (uint32_t c = 0; c < 4u; ++c) *reinterpret_cast<u32x4*>(V + at + c * 256u) = v[c];
     lds_barrier();
-    const bool vec = (((uintptr_t)out_k | (uintptr_t)out_v) & 15u) == 0;
     gu32* gk = gptr(out_k);
     gu32* gv = gptr(out_v);
 #pragma unroll
     for (uint32_t c = 0; c < 4u; ++c) {
         const uint32_t pos = at + c * 256u;
         const double* r = m + 4 * c;
-        if (vec && pos + 4u <= cnt) {
-            *reinterpret_cast<gu32x4*>(gk + pos) = u32x4{kt_key(r[0]) ^ flip_out, kt_key(r[1]) ^ flip_out,
+        if (pos + 4u <= cnt) {
+            *reinterpret_cast<gu32x4a4*>(gk + pos) = u32x4{kt_key(r[0]) ^ flip_out, kt_key(r[1]) ^ flip_out,
                                                          kt_key(r[2]) ^ flip_out, kt_key(r[3]) ^ flip_out};
-            *reinterpret_cast<gu32x4*>(gv + pos) =
+            *reinterpret_cast<gu32x4a4*>(gv + pos) =
                 u32x4{V[kt_tag(r[0])], V[kt_tag(r[1])], V[kt_tag(r[2])], V[kt_tag(r[3])]};
         } else {
 #pragma unroll

@@ -132,12 +132,11 @@ __global__ __launch_bounds__(W * 64, MINW) void k_merge_keys(Phase ph, Bufs b, R
         lds_barrier();
     }
     gu32* g = gptr(tr.dst_k) + obase;
-    const bool vec = ((uintptr_t)(tr.dst_k + obase) & 15u) == 0;
     row_put(o, m, lane, [&](int c, int step, uint32_t k0, uint32_t k1, uint32_t k2, uint32_t k3) {
         const u32x4 v{k0 ^ flip_out, k1 ^ flip_out, k2 ^ flip_out, k3 ^ flip_out};
         const uint32_t at = 4u * (uint32_t)(c + step);
-        if (vec && at + 4u <= cnt) {
-            *reinterpret_cast<gu32x4*>(g + at) = v;
+        if (at + 4u <= cnt) {
+            *reinterpret_cast<gu32x4a4*>(g + at) = v;
         } else {
 #pragma unroll
             for (uint32_t j = 0; j < 4u; ++j)

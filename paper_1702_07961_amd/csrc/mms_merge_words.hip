@@ -32,10 +32,7 @@ namespace {
 
 typedef double d2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-// two elements at an address aligned to one
-typedef uint32_t u32x2a4 __attribute__((ext_vector_type(2), aligned(4)));
 typedef const __attribute__((address_space(1))) u32x2a4 cgu32x2a4;
-typedef __attribute__((address_space(1))) u32x2 gu32x2;
 
 }  // namespace
 
@@ -169,12 +166,11 @@ __global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge_pairs(Phase 
     lds_barrier();
     gu32* ok = gptr(tr.dst_k) + obase;
     gu32* ov = gptr(tr.dst_v) + obase;
-    const bool vec = (((uintptr_t)(tr.dst_k + obase) | (uintptr_t)(tr.dst_v + obase)) & 7u) == 0;
     word_row_put(o, m, lane, [&](int c, int step, double a, double z) {
         const uint32_t at = 2u * (uint32_t)(c + step);
-        if (vec && at + 2u <= cnt) {
-            *reinterpret_cast<gu32x2*>(ok + at) = u32x2{kt_key(a) ^ flip_out, kt_key(z) ^ flip_out};
-            *reinterpret_cast<gu32x2*>(ov + at) = u32x2{V[kt_tag(a)], V[kt_tag(z)]};
+        if (at + 2u <= cnt) {
+            *reinterpret_cast<gu32x2a4*>(ok + at) = u32x2{kt_key(a) ^ flip_out, kt_key(z) ^ flip_out};
+            *reinterpret_cast<gu32x2a4*>(ov + at) = u32x2{V[kt_tag(a)], V[kt_tag(z)]};
         } else {
             if (at < cnt) {
                 ok[at] = kt_key(a) ^ flip_out;

@@ -132,13 +132,12 @@ struct Order64 {
 template <uint32_t NT>
 __device__ __forceinline__ void store_by_tags(uint64_t* out, const uint64_t* E, const uint32_t* tags, uint32_t cnt,
                                               uint64_t x, uint32_t tid) {
-    typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+    typedef uint64_t u64x2 __attribute__((ext_vector_type(2), aligned(8)));
     typedef __attribute__((address_space(1))) u64x2 gu64x2;
     gu64* g = gptr64(out);
-    const bool vec = ((uintptr_t)out & 15u) == 0;
     for (uint32_t c = tid; 2u * c < cnt; c += NT) {
         const uint32_t w = tags[c];
-        if (vec && 2u * c + 1u < cnt) {
+        if (2u * c + 1u < cnt) {
             *reinterpret_cast<gu64x2*>(g + 2u * c) = u64x2{E[w & 0xFFFFu] ^ x, E[w >> 16] ^ x};
         } else {
             g[2u * c] = E[w & 0xFFFFu] ^ x;
