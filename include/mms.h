@@ -194,13 +194,15 @@ int mms_copy_u32(const uint32_t* d_in, uint32_t* d_out, uint64_t n, void* stream
  * All segments advance together: one launch per kernel and phase covers
  * every segment's tiles (the base case, then per round the partition and
  * the merge).  The first call with a given (offsets, pointers, flags,
- * tuning) captures those launches into a hipGraph, and later calls with the
- * same signature replay it with a single graph launch on `stream`.
+ * tuning) plans it, and later calls with the same signature reuse the plan.
+ * With MMS_GRAPH=1 in the environment the launches are also captured into a
+ * hipGraph and replayed with a single graph launch on `stream`, which takes
+ * more host time than launching them.
  *
  * Memory: all device memory is the caller's.  The workspace holds the
  * ping-pong buffers, the partition table and the batch metadata (a 64-byte
  * descriptor per non-empty segment and 8 bytes per tile task).  The library
- * keeps, per captured signature (up to 8, least recently used evicted), a
+ * keeps, per signature (up to 8, least recently used evicted), a
  * host image of that metadata in pinned host memory, and every call copies
  * it into the workspace with an asynchronous copy on `stream` ahead of the
  * launches, so the workspace may be used for anything else between calls.
@@ -385,7 +387,7 @@ typedef enum {
     MMS_KERNEL_PARTITION = 1,  /* split indices (§4.1)      */
     MMS_KERNEL_MERGE = 2,      /* K-way merge (§4.2)        */
     MMS_KERNEL_COPY = 3,       /* bandwidth probe           */
-    MMS_KERNEL_SEGMENTED = 4,  /* one batched graph launch  */
+    MMS_KERNEL_SEGMENTED = 4,  /* all launches of one batch */
     MMS_KERNEL_KINDS = 5
 } mms_kernel_kind;
 

@@ -249,8 +249,8 @@ def segmented_sort(keys, offsets, values=None, out_keys=None, out_values=None, i
 
     ``offsets`` is a host sequence of num_segs+1 non-decreasing element
     offsets.  With ``values`` the sort is stable by key.  Returns ``out_keys``
-    (and ``out_values``).  The batch runs as one hipGraph launch per call once
-    the offsets and buffers repeat.
+    (and ``out_values``).  The batch is planned once for offsets and buffers
+    that repeat.
     """
     import numpy as np
     torch = _torch()

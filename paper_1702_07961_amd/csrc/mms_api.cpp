@@ -54,7 +54,7 @@ std::vector<TimingRec> g_recs;
 std::vector<hipEvent_t> g_pool;
 uint64_t g_launch[MMS_KERNEL_KINDS];
 double g_ms[MMS_KERNEL_KINDS];
-thread_local bool g_capturing = false;   // launches are being captured into a graph
+thread_local bool g_capturing = false;   // launches are captured into a graph, or timed as one batch
 
 hipEvent_t take_event() {
     if (!g_pool.empty()) {
@@ -529,39 +529,70 @@ struct SegPlan {
     uint64_t off_vals, off_table, off_meta, seg_bytes, meta_bytes, ws_bytes;
 };
 
-int make_seg_plan(const uint64_t* off, uint64_t ns, uint32_t flags, SegPlan& sp) {
-    sp.pairs = (flags & MMS_PAIRS) != 0;
-    sp.total = off[ns];
+// The checks and the launch parameters of a batch, from its offsets alone.
+struct SegShape {
+    uint64_t count = 0;   // non-empty segments
+    Tune tune{};
+};
+
+int seg_shape(const uint64_t* off, uint64_t ns, bool pairs, SegShape& sh) {
     uint64_t maxn = 0;
-    sp.seg_off.clear();
-    sp.seg_n.clear();
     for (uint64_t s = 0; s < ns; ++s) {
         if (off[s + 1] < off[s]) return fail(MMS_EINVAL, "offsets decrease at segment %llu", (unsigned long long)s);
         const uint64_t n = off[s + 1] - off[s];
         maxn = std::max<uint64_t>(maxn, n);
+        sh.count += n ? 1u : 0u;
+    }
+    if (maxn >= (1ull << 32)) return fail(MMS_EINVAL, "a segment holds 2^32 or more elements");
+    sh.tune = tune_for_batch(off[ns], sh.count, maxn, pairs);
+    return MMS_OK;
+}
+
+void make_seg_plan(const uint64_t* off, uint64_t ns, bool pairs, const Tune& tune, SegPlan& sp) {
+    sp.pairs = pairs;
+    sp.total = off[ns];
+    sp.seg_off.clear();
+    sp.seg_n.clear();
+    for (uint64_t s = 0; s < ns; ++s) {
+        const uint64_t n = off[s + 1] - off[s];
         if (n) {
             sp.seg_off.push_back(off[s]);
             sp.seg_n.push_back(n);
         }
     }
-    if (maxn >= (1ull << 32)) return fail(MMS_EINVAL, "a segment holds 2^32 or more elements");
-    build_batch_tasks(sp.seg_n.data(), sp.seg_n.size(), sp.pairs, tune_for_batch(sp.total, sp.seg_n.size(), maxn, sp.pairs),
-                      sp.bt);
+    build_batch_tasks(sp.seg_n.data(), sp.seg_n.size(), sp.pairs, tune, sp.bt);
     sp.off_vals = align_up(sp.total * 4);
     sp.off_table = sp.off_vals + (sp.pairs ? align_up(sp.total * 4) : 0);
     sp.off_meta = sp.off_table + sp.bt.table_bytes();
     sp.seg_bytes = align_up(sp.seg_n.size() * sizeof(mms::SegDesc));
     sp.meta_bytes = align_up(sp.seg_bytes + sp.bt.ntasks * sizeof(mms::TileTask));
     sp.ws_bytes = sp.off_meta + sp.meta_bytes;
-    return MMS_OK;
 }
 
-// A captured batch, keyed by offsets, pointers and tuning: the host image of
+// The workspace of make_seg_plan's plan without its task lists.
+uint64_t seg_ws_bytes(const uint64_t* off, uint64_t ns, bool pairs, const SegShape& sh) {
+    std::vector<uint64_t> tiles;   // per phase
+    for (uint64_t s = 0; s < ns; ++s) add_segment_tiles(off[s + 1] - off[s], sh.tune, tiles);
+    uint64_t ntasks = 0;
+    BatchTasks bt;
+    bt.tune = sh.tune;
+    bt.phases.resize(tiles.size());
+    for (size_t r = 0; r < tiles.size(); ++r) {
+        ntasks += tiles[r];
+        if (r) bt.max_round_tiles = std::max(bt.max_round_tiles, tiles[r]);
+    }
+    return align_up(off[ns] * 4) * (pairs ? 2u : 1u) + bt.table_bytes() +
+           align_up(align_up(sh.count * sizeof(mms::SegDesc)) + ntasks * sizeof(mms::TileTask));
+}
+
+// A planned batch, keyed by offsets, pointers and tuning: the host image of
 // its metadata in pinned host memory the library owns (uploaded into the
 // caller's workspace by an asynchronous copy on the caller's stream before
-// every launch), and the instantiated graph of all kernel launches.  The
-// event is recorded after each launch, so an entry is torn down only after
-// the last work that reads its image or runs its graph has finished.
+// every launch), and with MMS_GRAPH=1 the instantiated graph of all kernel
+// launches.  The event is recorded after each launch, so an entry is torn down
+// only after the last work that reads its image or runs its graph has
+// finished.  An entry whose launches a caller captured stays: the captured
+// copy reads its image whenever it is replayed.
 struct SegEntry {
     std::string key;
     SegPlan plan;
@@ -569,6 +600,7 @@ struct SegEntry {
     hipEvent_t last_use = nullptr;
     hipGraphExec_t exec = nullptr;
     hipGraph_t graph = nullptr;
+    bool captured = false;
 };
 
 std::mutex g_seg_mu;
@@ -601,10 +633,15 @@ std::string seg_key(const uint64_t* off, uint64_t ns, uint32_t flags, const void
     return k;
 }
 
+// A batch is at most 1 + 2 R launches of one to four microseconds of host time
+// each; launched as a graph they take longer (host time a call, graph and
+// launches: 4096 segments of 2^6 to 2^12 keys, one launch, 60 and 35 us; 300 of
+// 2^8 to 2^16, five, 137 and 25 us), so the graph is built on request only.
 bool seg_graph_enabled() {
     static const bool on = [] {
-        const char* s = getenv("MMS_NO_GRAPH");
-        return !(s && atoi(s) != 0);
+        const char* no = getenv("MMS_NO_GRAPH");
+        const char* yes = getenv("MMS_GRAPH");
+        return yes && atoi(yes) != 0 && !(no && atoi(no) != 0);
     }();
     return on;
 }
@@ -615,18 +652,23 @@ int segmented_impl(const uint32_t* kin, uint32_t* kout, const uint32_t* vin, uin
     if (flags & ~(MMS_KEY_I32 | MMS_PAIRS)) return fail(MMS_EINVAL, "unknown flags 0x%x", flags);
     if (ns == 0) return MMS_OK;
     if (!off) return fail(MMS_EINVAL, "null offsets");
-    SegPlan sp;
-    int rc = make_seg_plan(off, ns, flags | (pairs ? MMS_PAIRS : 0u), sp);
+    SegShape sh;
+    int rc = seg_shape(off, ns, pairs, sh);
     if (rc) return rc;
-    if (sp.seg_n.empty()) return MMS_OK;
-    rc = check_buffers(kin, vin, kout, vout, sp.total, ws, sp.ws_bytes, ws_bytes);
-    if (rc) return rc;
+    if (sh.count == 0) return MMS_OK;
 
     const void* ptrs[5] = {kin, kout, vin, vout, ws};
-    const std::string key = seg_key(off, ns, flags | (pairs ? MMS_PAIRS : 0u), ptrs, 5, sp.bt.tune);
+    const std::string key = seg_key(off, ns, flags | (pairs ? MMS_PAIRS : 0u), ptrs, 5, sh.tune);
     std::lock_guard<std::mutex> lock(g_seg_mu);
     auto it = std::find_if(g_seg_cache.begin(), g_seg_cache.end(), [&](const SegEntry& e) { return e.key == key; });
-    if (it == g_seg_cache.end()) {
+    if (it != g_seg_cache.end()) {
+        rc = check_buffers(kin, vin, kout, vout, it->plan.total, ws, it->plan.ws_bytes, ws_bytes);
+        if (rc) return rc;
+    } else {
+        SegPlan sp;
+        make_seg_plan(off, ns, pairs, sh.tune, sp);
+        rc = check_buffers(kin, vin, kout, vout, sp.total, ws, sp.ws_bytes, ws_bytes);
+        if (rc) return rc;
         SegEntry e;
         e.key = key;
         e.plan = std::move(sp);
@@ -660,12 +702,18 @@ int segmented_impl(const uint32_t* kin, uint32_t* kout, const uint32_t* vin, uin
             at += v.size() * sizeof(mms::TileTask);
         }
         g_seg_cache.push_front(std::move(e));
-        while (g_seg_cache.size() > kSegCacheMax) {
-            drop_entry(g_seg_cache.back());
-            g_seg_cache.pop_back();
+        size_t kept = 0;
+        for (auto i = g_seg_cache.begin(); i != g_seg_cache.end();) {
+            if (i->captured || ++kept <= kSegCacheMax) {
+                ++i;
+            } else {
+                drop_entry(*i);
+                i = g_seg_cache.erase(i);
+            }
         }
         it = g_seg_cache.begin();
-    } else if (it != g_seg_cache.begin()) {
+    }
+    if (it != g_seg_cache.begin()) {
         g_seg_cache.splice(g_seg_cache.begin(), g_seg_cache, it);
         it = g_seg_cache.begin();
     }
@@ -679,11 +727,20 @@ int segmented_impl(const uint32_t* kin, uint32_t* kout, const uint32_t* vin, uin
     // the metadata goes into the caller's workspace on the caller's stream,
     // ahead of the launches that read it (every call: the caller may have
     // used the workspace for something else in between)
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    (void)hipStreamIsCapturing(s, &cs);
+    const bool capturing = cs == hipStreamCaptureStatusActive;
+    if (capturing) e.captured = true;
     hipError_t ue = hipMemcpyAsync(d_meta, e.h_meta, p.meta_bytes, hipMemcpyHostToDevice, s);
     if (ue != hipSuccess) return hip_fail(ue, "batch metadata upload");
-    if (!seg_graph_enabled()) {
-        rc = run_batch(p.bt, d_segs, d_tasks, table, flip, s);
-        const hipError_t ee = hipEventRecord(e.last_use, s);
+    if (capturing || !seg_graph_enabled()) {
+        {
+            Timed tm(MMS_KERNEL_SEGMENTED, s);
+            set_capturing(true);   // timed as one
+            rc = run_batch(p.bt, d_segs, d_tasks, table, flip, s);
+            set_capturing(false);
+        }
+        const hipError_t ee = capturing ? hipSuccess : hipEventRecord(e.last_use, s);
         if (rc) return rc;
         return ee == hipSuccess ? MMS_OK : hip_fail(ee, "batch event");
     }
@@ -817,9 +874,10 @@ int mms_sort_pairs_u32(const uint32_t* d_kin, const uint32_t* d_vin, uint32_t* d
 
 size_t mms_segmented_workspace_bytes(const uint64_t* h_offsets, uint64_t num_segs, uint32_t flags) {
     if (!h_offsets || num_segs == 0) return 0;
-    SegPlan sp;
-    if (make_seg_plan(h_offsets, num_segs, flags, sp)) return 0;
-    return sp.seg_n.empty() ? 0 : (size_t)sp.ws_bytes;
+    SegShape sh;
+    const bool pairs = (flags & MMS_PAIRS) != 0;
+    if (seg_shape(h_offsets, num_segs, pairs, sh)) return 0;
+    return sh.count ? (size_t)seg_ws_bytes(h_offsets, num_segs, pairs, sh) : 0;
 }
 
 int mms_segmented_sort(const uint32_t* d_kin, uint32_t* d_kout, const uint32_t* d_vin, uint32_t* d_vout,
