@@ -17,9 +17,17 @@ template <uint32_t S>
 __device__ __forceinline__ LoadSteps load_steps(const PieceLayout& pc, uint32_t s, uint32_t Kg, uint64_t L, int lane) {
     const uint32_t own = (pc.len + (1u << S) - 1u) >> S;   // lanes k < Kg hold piece k, the others none
     const uint32_t before = excl_scan16(own);
+    // pieces whose steps end at or before this lane's: of the sorted ends (16 at
+    // most), how many of every fourth, then how many of the three up to the next
+    const uint32_t end = before + own;
     uint32_t k = 0;
-    for (uint32_t j = 0; j + 1u < Kg; ++j)   // pieces whose steps end at or before this lane's
-        k += (uint32_t)__builtin_amdgcn_readlane((int)(before + own), (int)j) <= (uint32_t)lane ? 1u : 0u;
+#pragma unroll
+    for (int j = 3; j < 15; j += 4) k += (uint32_t)__builtin_amdgcn_readlane((int)end, j) <= (uint32_t)lane ? 4u : 0u;
+    const int k4 = (int)(k << 2);
+    const uint32_t e0 = (uint32_t)__builtin_amdgcn_ds_bpermute(k4, (int)end);
+    const uint32_t e1 = (uint32_t)__builtin_amdgcn_ds_bpermute(k4 + 4, (int)end);
+    const uint32_t e2 = (uint32_t)__builtin_amdgcn_ds_bpermute(k4 + 8, (int)end);
+    k += (e0 <= (uint32_t)lane ? 1u : 0u) + (e1 <= (uint32_t)lane ? 1u : 0u) + (e2 <= (uint32_t)lane ? 1u : 0u);
     const uint32_t from = (uint32_t)((uint64_t)(uint32_t)lane * L) + s;   // lane k: piece k's first element
     auto of = [&](uint32_t x) { return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(k << 2), (int)x); };
     const uint32_t at = ((uint32_t)lane - of(before)) << S;
@@ -27,7 +35,7 @@ __device__ __forceinline__ LoadSteps load_steps(const PieceLayout& pc, uint32_t 
     r.src = of(from) + at;
     r.dst = of(pc.sb) + at;
     r.cnt = min(of(pc.len) - at, 1u << S);   // meaningful below total only
-    r.total = (uint32_t)__builtin_amdgcn_readlane((int)(before + own), (int)(Kg - 1u));
+    r.total = (uint32_t)__builtin_amdgcn_readlane((int)end, 15);
     return r;
 }
 

@@ -37,11 +37,6 @@ namespace mms {
 template <int EM> constexpr uint32_t kWordItemChunks = 8u * EM - 2u;
 
 // ---- items --------------------------------------------------------------------
-// Item words, in chunks: word 0 = first chunk of the pair's run A (bits
-// 0..11) and of run B (12..23); word 1 = end of run B (0..11), first output
-// of the item inside the pair (12..23), outputs (24..31, 0: no item).  After
-// the items, for each pair (8, 4, 2 and 1), the items of its level up to its
-// end.
 template <int EM, uint32_t TOUT, int W>
 struct WordItems {
     static constexpr uint32_t kCap = TOUT + 4u * kMaxFanout;    // LDS slots of a tile
@@ -53,41 +48,8 @@ struct WordItems {
     static_assert(kCap / 2u < 4096u, "chunk numbers take 12 bits");
     static_assert((kCap / 2u + kWordItemChunks<EM> - 1u) / kWordItemChunks<EM> <= kRows, "a pass holds any pair");
 
-    // The items of every level of a tile (one wave).  Lane q < 15 takes pair p
-    // of level l (8, 4, 2 and 1 pairs): the fewest items that hold it, in
-    // equal shares; the items of one pair are then written by as many lanes.
-    // sbeg: first slots of the pieces, sbeg[Kg] the end.
     __device__ static __forceinline__ void build(uint32_t* items, const uint32_t* sbeg, uint32_t Kg, int lane) {
-        const uint32_t q = (uint32_t)lane;
-        const uint32_t l = q < 8u ? 0u : q < 12u ? 1u : q < 14u ? 2u : 3u;
-        const uint32_t p = q < 8u ? q : q < 12u ? q - 8u : q < 14u ? q - 12u : 0u;
-        const uint32_t a = sbeg[min((2u * p) << l, Kg)] >> 1;
-        const uint32_t b = sbeg[min((2u * p + 1u) << l, Kg)] >> 1;
-        const uint32_t e = sbeg[min((2u * p + 2u) << l, Kg)] >> 1;
-        const uint32_t size = q < 15u ? e - a : 0u;
-        const uint32_t nit = udiv_small(size + kWordItemChunks<EM> - 1u, kWordItemChunks<EM>);
-        const uint32_t share = nit ? udiv_small(size + nit - 1u, nit) : 0u;
-        const uint32_t before = excl_scan16(nit);
-        const uint32_t lv0 = l == 0u ? 0u : l == 1u ? 8u : l == 2u ? 12u : 14u;
-        const uint32_t first = before - (uint32_t)__builtin_amdgcn_ds_bpermute((int)(lv0 << 2), (int)before);
-        const uint32_t w0 = a | (b << 12);
-#pragma unroll 1
-        for (uint32_t s = 0; s < 15u; ++s) {
-            const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)nit, (int)s);
-            const uint32_t f = (uint32_t)__builtin_amdgcn_readlane((int)first, (int)s);
-            const uint32_t sh = (uint32_t)__builtin_amdgcn_readlane((int)share, (int)s);
-            const uint32_t sz = (uint32_t)__builtin_amdgcn_readlane((int)size, (int)s);
-            const uint32_t ww = (uint32_t)__builtin_amdgcn_readlane((int)w0, (int)s);
-            const uint32_t en = (uint32_t)__builtin_amdgcn_readlane((int)e, (int)s);
-            const uint32_t lv = s < 8u ? 0u : s < 12u ? 1u : s < 14u ? 2u : 3u;
-            if (q < n) {
-                const uint32_t d0 = q * sh;
-                const uint32_t cnt = sz > d0 ? min(sh, sz - d0) : 0u;
-                uint32_t* it = items + 2u * (lv * kPerLevel + f + q);
-                *reinterpret_cast<uint2*>(it) = make_uint2(ww, en | (d0 << 12) | (cnt << 24));
-            }
-        }
-        if (q < 15u) items[4u * kPerLevel * 2u + q] = first + nit;
+        build_items<1, kWordItemChunks<EM>, kPerLevel>(items, sbeg, Kg, lane);
     }
 };
 
