@@ -75,22 +75,24 @@ __global__ __launch_bounds__(W * 64, MINW) void k_merge_keys(Phase ph, Bufs b, R
     }
     const PieceLayout pc = piece_layout(s, e, Kg, cnt, lane);
     const LoadSteps st = load_steps<8>(pc, s, Kg, L, lane);
-    static_assert(TMAX / 256u + kMaxFanout <= 64u, "a step per lane");
+    static_assert(TMAX / 256u + kMaxFanout < 64u, "a step per lane, and one lane without");
     cgu32* gk = gptr(tr.src_k) + gb;
-    const uint32_t glast = (uint32_t)glen - 4u;   // a group of two runs or more holds more than a base tile
-    constexpr uint32_t U = W == 8 ? 4 : 3;   // steps a wave has in flight
+    // A step reads 256 keys from its first on: a group of two runs or more holds
+    // more than that, and the steps of its last ones come after the others, key
+    // by key.  Steps past the last one read the group's first keys and store
+    // nothing; lane 63 has none (above).
+    const uint32_t gend = (uint32_t)glen - 256u;
+    const bool late = (uint32_t)lane < st.total && st.src > gend;
+    const uint32_t src = (uint32_t)lane < st.total ? min(st.src, gend) : 0u;
+    const int len = (uint32_t)lane < st.total && !late ? (int)st.cnt : 0;
+    constexpr uint32_t U = W == 8 ? 5 : 3;   // steps a wave has in flight
     for (uint32_t e0 = (uint32_t)wave; e0 < st.total; e0 += U * W) {
         u32x4a4 v[U];
-        uint32_t dst[U];
-        int left[U];   // keys from the lane's first slot to the step's end; bits 30, 31: keys read too early
 #pragma unroll
-        for (uint32_t u = 0; u < U; ++u) {   // steps past the last one load it again and store nothing
-            const uint32_t x = min(e0 + u * W, st.total - 1u);
-            const uint32_t q = (uint32_t)__builtin_amdgcn_readlane((int)st.src, (int)x) + 4u * (uint32_t)lane;
-            const uint32_t qc = min(q, glast);   // the group's last keys are read up to three early
-            v[u] = *reinterpret_cast<cgu32x4a4*>(gk + qc);
-            dst[u] = ((uint32_t)__builtin_amdgcn_readlane((int)st.dst, (int)x) + 4u * (uint32_t)lane) | (q - qc) << 16;
-            left[u] = e0 + u * W < st.total ? __builtin_amdgcn_readlane((int)st.cnt, (int)x) - 4 * lane : 0;
+        for (uint32_t u = 0; u < U; ++u) {
+            const int x = (int)min(e0 + u * W, 63u);
+            const uint32_t from = (uint32_t)__builtin_amdgcn_readlane((int)src, x);
+            v[u] = *reinterpret_cast<cgu32x4a4*>(gk + from + 4u * (uint32_t)lane);
         }
         if (e0 == 0u) {   // wave 0 plans the levels while its first loads are in flight
             if ((uint32_t)lane < Kg) sbeg[lane] = pc.sb;
@@ -103,21 +105,24 @@ __global__ __launch_bounds__(W * 64, MINW) void k_merge_keys(Phase ph, Bufs b, R
         }
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) {
-            if (left[u] <= 0) continue;
-            u32x4 k = v[u];
-            const uint32_t back = dst[u] >> 16;
-            if (back) {   // key j of the chunk is component j + back
-                k.x = back == 1u ? k.y : back == 2u ? k.z : k.w;
-                k.y = back == 1u ? k.z : k.w;
-                k.z = k.w;
+            const int x = (int)min(e0 + u * W, 63u);
+            const int left = __builtin_amdgcn_readlane(len, x) - 4 * lane;
+            const uint32_t dst = (uint32_t)__builtin_amdgcn_readlane((int)st.dst, x) + 4u * (uint32_t)lane;
+            if (left > 0) {   // slots past the piece hold the largest key
+                u32x4 k = v[u];
+                k.y = left < 2 ? kSentKey : k.y;
+                k.z = left < 3 ? kSentKey : k.z;
+                k.w = left < 4 ? kSentKey : k.w;
+                *reinterpret_cast<u32x4*>(X + dst) = k;
             }
-            if (left[u] < 4) {   // slots past the piece hold the largest key
-                k.w = kSentKey;
-                if (left[u] < 3) k.z = kSentKey;
-                if (left[u] < 2) k.y = kSentKey;
-            }
-            *reinterpret_cast<u32x4*>(X + (dst[u] & 0xFFFFu)) = k;
         }
+    }
+    for (uint64_t todo = __ballot(late); todo; todo &= todo - 1u) {
+        const int x = __builtin_ctzll(todo);
+        const uint32_t from = (uint32_t)__builtin_amdgcn_readlane((int)st.src, x);
+        const uint32_t dst = (uint32_t)__builtin_amdgcn_readlane((int)st.dst, x);
+        const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)st.cnt, x);
+        for (uint32_t j = threadIdx.x; j < ((n + 3u) & ~3u); j += W * 64u) X[dst + j] = j < n ? gk[from + j] : kSentKey;
     }
     lds_barrier();
 
@@ -164,7 +169,8 @@ static hipError_t launch_variant(const Phase& ph, const Bufs& b, const RoundArgs
 
 hipError_t launch_merge_keys(const Phase& ph, const Bufs& b, const RoundArgs& ra, const uint32_t* table,
                              uint32_t flip, int variant, hipStream_t s) {
-    if (ra.Tout > kToutKeys || ra.K > kMaxFanout || ra.Tout % 4 || ra.L % 4) return hipErrorInvalidValue;
+    if (ra.Tout > kToutKeys || ra.K > kMaxFanout || ra.Tout % 4 || ra.L % 4 || ra.L < 256)
+        return hipErrorInvalidValue;
     if (ph.tiles == 0) return hipSuccess;
     if (variant == 4) return launch_merge_heap(ph, b, ra, table, flip, s);
     // a pass of rows holds any pair: eight waves of 256-key blocks up to
