@@ -99,23 +99,24 @@ __global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge_pairs(Phase 
     }
     const PieceLayout pc = piece_layout(s, e, Kg, cnt, lane);
     const LoadSteps st = load_steps<7>(pc, s, Kg, L, lane);
-    static_assert(TOUT / 128u + kMaxFanout <= 64u, "a step per lane");
+    static_assert(TOUT / 128u + kMaxFanout < 64u, "a step per lane, and one lane without");
     cgu32* gk = gptr(tr.src_k) + gb;
-    const uint32_t glast = (uint32_t)glen - 2u;   // a group of two runs or more holds more than a base tile
-    constexpr uint32_t U = 32 / W;                   // steps a wave has in flight
+    // A step reads 128 keys from its first on: a group of two runs or more holds
+    // more than that, and the steps of its last ones come after the others, key
+    // by key.  Steps past the last one read the group's first keys and store
+    // nothing; lane 63 has none (above).
+    const uint32_t gend = (uint32_t)glen - 128u;
+    const bool late = (uint32_t)lane < st.total && st.src > gend;
+    const uint32_t src = (uint32_t)lane < st.total ? min(st.src, gend) : 0u;
+    const int len = (uint32_t)lane < st.total && !late ? (int)st.cnt : 0;
+    constexpr uint32_t U = 40 / W;                   // steps a wave has in flight
     for (uint32_t e0 = (uint32_t)wave; e0 < st.total; e0 += U * W) {
         u32x2 kv[U];
-        uint32_t dst[U], left[U], back[U];
 #pragma unroll
-        for (uint32_t u = 0; u < U; ++u) {   // steps past the last one load it again and store nothing
-            const uint32_t x = min(e0 + u * W, st.total - 1u);
-            const uint32_t src = (uint32_t)__builtin_amdgcn_readlane((int)st.src, (int)x);
-            const uint32_t q = src + 2u * (uint32_t)lane;
-            const uint32_t qc = min(q, glast);   // the group's last element is read one early
-            back[u] = q - qc;
-            kv[u] = *reinterpret_cast<cgu32x2a4*>(gk + qc);
-            dst[u] = (uint32_t)__builtin_amdgcn_readlane((int)st.dst, (int)x) + 2u * (uint32_t)lane;
-            left[u] = e0 + u * W < st.total ? (uint32_t)__builtin_amdgcn_readlane((int)st.cnt, (int)x) : 0u;
+        for (uint32_t u = 0; u < U; ++u) {
+            const int x = (int)min(e0 + u * W, 63u);
+            const uint32_t from = (uint32_t)__builtin_amdgcn_readlane((int)src, x);
+            kv[u] = *reinterpret_cast<cgu32x2a4*>(gk + from + 2u * (uint32_t)lane);
         }
         if (e0 == 0u) {   // wave 0 plans the levels while its first loads are in flight
             if ((uint32_t)lane < Kg) sbeg[lane] = pc.sb;
@@ -130,14 +131,23 @@ __global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge_pairs(Phase 
         }
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) {
-            const uint32_t l2 = 2u * (uint32_t)lane;
-            if (l2 < ((left[u] + 3u) & ~3u)) {   // slots past the piece hold the sentinel
-                const uint32_t k0 = back[u] ? kv[u].y : kv[u].x;
-                const double w0 = l2 < left[u] ? kt_pack(k0, dst[u]) : kt_sentinel();
-                const double w1 = l2 + 1u < left[u] ? kt_pack(kv[u].y, dst[u] + 1u) : kt_sentinel();
-                *reinterpret_cast<d2*>(X + dst[u]) = d2{w0, w1};
+            const int x = (int)min(e0 + u * W, 63u);
+            const int n = __builtin_amdgcn_readlane(len, x), left = n - 2 * lane;
+            const uint32_t dst = (uint32_t)__builtin_amdgcn_readlane((int)st.dst, x) + 2u * (uint32_t)lane;
+            if (2 * lane < ((n + 3) & ~3)) {   // slots past the piece hold the sentinel
+                const double w0 = left > 0 ? kt_pack(kv[u].x, dst) : kt_sentinel();
+                const double w1 = left > 1 ? kt_pack(kv[u].y, dst + 1u) : kt_sentinel();
+                *reinterpret_cast<d2*>(X + dst) = d2{w0, w1};
             }
         }
+    }
+    for (uint64_t todo = __ballot(late); todo; todo &= todo - 1u) {
+        const int x = __builtin_ctzll(todo);
+        const uint32_t from = (uint32_t)__builtin_amdgcn_readlane((int)st.src, x);
+        const uint32_t dst = (uint32_t)__builtin_amdgcn_readlane((int)st.dst, x);
+        const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)st.cnt, x);
+        for (uint32_t j = threadIdx.x; j < ((n + 3u) & ~3u); j += W * 64u)
+            X[dst + j] = j < n ? kt_pack(gk[from + j], dst + j) : kt_sentinel();
     }
     lds_barrier();
 
@@ -373,7 +383,7 @@ __global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge64(Phase64 ph
 hipError_t launch_merge_pairs(const Phase& ph, const Bufs& b, const RoundArgs& ra, const uint32_t* table,
                               uint32_t flip, hipStream_t s) {
     if (ph.tiles == 0) return hipSuccess;
-    if (ra.Tout > kToutPairs || ra.Tout % 4 || ra.K > kMaxFanout) return hipErrorInvalidValue;
+    if (ra.Tout > kToutPairs || ra.Tout % 4 || ra.K > kMaxFanout || ra.L < 128) return hipErrorInvalidValue;
     // Up to as many tiles as are resident at once, one workgroup's latency is
     // what counts, and eight waves of 128-word blocks take half as long over a
     // level: 3.0e5 uniform pairs 79.1 us with the larger blocks and 71.1 with
