@@ -227,12 +227,13 @@ int mms_segmented_sort(const uint32_t* d_kin, uint32_t* d_kout, const uint32_t* 
  * otherwise).
  *   fanout      merge fan-out K (power of two, 2..16)
  *   merge_tile  keys-only merge output tile (multiple of 256, 1024..8192;
- *               key-value merges use 4096 whatever the entry says)
- *   variant     keys-only merge kernel shape (0 and 3: 8 waves, 256-key
- *               blocks of 16 lanes; 1: the same with 16 waves; 2: 8 waves,
- *               128-key blocks for merge tiles up to 4096 (256-key blocks
- *               above); 4: the minBlockHeap of §4.2, one heap of 64-key
- *               nodes per wave and one merge tile per wave)
+ *               key-value merges use 3840 whatever the entry says)
+ *   variant     keys-only merge kernel shape (1: 16 waves, 128-key blocks
+ *               of 16 lanes, for merge tiles up to 7424; 2: 8 waves, 128-key
+ *               blocks, up to 3584; 0, 3 and what those do not hold: 256-key
+ *               blocks, 8 waves up to 7680 and 16 above; 4: the minBlockHeap
+ *               of §4.2, one heap of 64-key nodes per wave and one merge tile
+ *               per wave)
  *   base        base-case shape, keys per lane x waves (§4.3's base case
  *               sorts one tile per workgroup): 0: 8 x 4, 1: 4 x 8, 2: 16 x 2,
  *               all 2048-key tiles; 3: 8 x 8 and 5: 16 x 4, 4096-key tiles;

@@ -7,7 +7,7 @@ shape) with HIP events and keeps the fastest; with those fixed it then times
 each base-case shape (keys per lane x waves, and with it the base tile of
 2048, 4096 or 8192 keys).  Key-value sorts get entries of their own: the
 stable sort of n (uint32 key, index) pairs under every fan-out and key-value
-base shape (8 x 4, 8 x 8).  The table is written as JSON.
+base shape (8 x 4, 8 x 8, 16 x 4).  The table is written as JSON.
 The package loads that table into the library (mms_set_tuning) the first
 time the library is used.
 

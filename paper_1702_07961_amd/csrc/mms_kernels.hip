@@ -277,7 +277,7 @@ __global__ __launch_bounds__(W * 64) void k_tile_sort_pairs(Phase ph, Bufs b, ui
 // cycles, VALU 68 %; 4096-pair tiles of 2^27 pairs 608 us, 8 x 8 1448.
 // ===========================================================================
 template <int W>
-__global__ __launch_bounds__(W * 64, 8) void k_tile_net_keys(Phase ph, Bufs b, uint32_t flip) {
+__global__ __launch_bounds__(W * 64, 8) void k_tile_sort_net_keys(Phase ph, Bufs b, uint32_t flip) {
     constexpr uint32_t T = 1024u * W;
     __shared__ __align__(16) uint32_t X[net_words<uint32_t>(T)];
     const int lane = threadIdx.x & 63;
@@ -324,7 +324,7 @@ __global__ __launch_bounds__(W * 64, 8) void k_tile_net_keys(Phase ph, Bufs b, u
 // Pairs: words (key, tile position); the values wait in registers and take the
 // words' place in LDS at the end, to be gathered by tag.
 template <int W>
-__global__ __launch_bounds__(W * 64, 4) void k_tile_net_pairs(Phase ph, Bufs b, uint32_t flip) {
+__global__ __launch_bounds__(W * 64, 4) void k_tile_sort_net_pairs(Phase ph, Bufs b, uint32_t flip) {
     constexpr uint32_t T = 1024u * W;
     __shared__ __align__(16) double X[net_words<double>(T)];
     const int lane = threadIdx.x & 63;
@@ -507,10 +507,10 @@ template <int W>
 static hipError_t launch_tile_net(bool pairs, const Phase& ph, const Bufs& b, uint32_t flip, hipStream_t s) {
     const dim3 grid((unsigned)ph.tiles), block(W * 64);
     if (pairs) {
-        if constexpr (W <= 4) hipLaunchKernelGGL((k_tile_net_pairs<W>), grid, block, 0, s, ph, b, flip);
+        if constexpr (W <= 4) hipLaunchKernelGGL((k_tile_sort_net_pairs<W>), grid, block, 0, s, ph, b, flip);
         else return hipErrorInvalidValue;
     } else {
-        hipLaunchKernelGGL((k_tile_net_keys<W>), grid, block, 0, s, ph, b, flip);
+        hipLaunchKernelGGL((k_tile_sort_net_keys<W>), grid, block, 0, s, ph, b, flip);
     }
     return hipGetLastError();
 }

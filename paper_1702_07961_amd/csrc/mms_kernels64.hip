@@ -30,7 +30,7 @@ namespace mms {
 // 310 us against one of keys and tags (2048-pair tiles).
 // ===========================================================================
 template <int W, bool PAIRS>
-__global__ __launch_bounds__(W * 64, 3) void k_tile_net64(Phase64 ph, Bufs64 b, uint64_t flip) {
+__global__ __launch_bounds__(W * 64, 3) void k_tile_sort_net64(Phase64 ph, Bufs64 b, uint64_t flip) {
     constexpr uint32_t T = 1024u * W, NT = W * 64u;
     static_assert(T <= 1u << kSlotBits, "slots");
     __shared__ struct __align__(16) {
@@ -166,8 +166,8 @@ hipError_t launch_tile_sort64(bool pairs, const Phase64& ph, const Bufs64& b, ui
     if (ph.tiles == 0) return hipSuccess;
     constexpr int W = kT64Waves;
     const dim3 grid((unsigned)ph.tiles), block(W * 64);
-    if (pairs) hipLaunchKernelGGL((k_tile_net64<W, true>), grid, block, 0, s, ph, b, flip);
-    else hipLaunchKernelGGL((k_tile_net64<W, false>), grid, block, 0, s, ph, b, flip);
+    if (pairs) hipLaunchKernelGGL((k_tile_sort_net64<W, true>), grid, block, 0, s, ph, b, flip);
+    else hipLaunchKernelGGL((k_tile_sort_net64<W, false>), grid, block, 0, s, ph, b, flip);
     return hipGetLastError();
 }
 
