@@ -9,10 +9,10 @@
 // the others merge while one loads.
 //
 // Bound by VALU issue: it issues in all of the launch's cycles (LDS busy in
-// half of them).  10^8 keys, K = 16, 7424-key tiles: 252 us per launch on
-// average; as a persistent kernel of two workgroups per compute unit that
-// loaded the next tile into registers and a second buffer meanwhile, 297 with
-// VALU in 75 % of the cycles.
+// half of them).  10^8 keys, K = 16, 7424-key tiles: 248 us per launch on
+// average, 3.2 TB/s; as a persistent kernel of two workgroups per compute unit
+// that loaded the next tile into registers and a second buffer meanwhile, 297
+// with VALU in 75 % of the cycles.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -128,10 +128,11 @@ __global__ __launch_bounds__(W * 64, MINW) void k_merge_keys(Phase ph, Bufs b, R
 
     uint32_t nlev = 0;
     while ((1u << nlev) < Kg) ++nlev;
+    const bool empty = __popcll(__ballot(pc.len != 0u)) < 1 << nlev;   // some pairs may have one run only
     uint32_t m[EM];
     RowOut o;
     for (uint32_t lvl = 0;;) {
-        row_merge_level<EM, Items>(X, items, lvl, sent, wscr, wave, lane, m, o);
+        row_merge_level<EM, Items>(X, items, lvl, sent, wscr, wave, lane, empty && lvl + 1u < nlev, m, o);
         if (++lvl == nlev) break;
         row_put_lds(X, o, m, lane);
         lds_barrier();

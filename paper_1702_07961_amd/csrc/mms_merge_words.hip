@@ -39,7 +39,7 @@ typedef const __attribute__((address_space(1))) u32x2a4 cgu32x2a4;
 // Bound by VALU issue (74 % of the launch's cycles; LDS half of them).  LDS
 // holds one 8-byte word per element and nothing else that grows with the tile,
 // so four workgroups of four waves share a compute unit.  2^27 pairs, K = 16:
-// 0.81 ms per launch on average, where 512-pair blocks of a wave (two level
+// 0.81 ms per launch on average when it was written (0.72 now), where 512-pair blocks of a wave (two level
 // buffers of keys and tags, the values in LDS throughout, two workgroups of
 // eight waves) took 1.06.  With the values in LDS throughout and all lane
 // distances by DPP, three workgroups fit: 0.92.
@@ -239,7 +239,7 @@ __device__ __forceinline__ void load_u64(const uint64_t* base, uint32_t glast, c
 
 // Bound by VALU issue like the merge above.  Launch average of a sort, against
 // blocks of 64-bit keys in their own order (a compare and four selects per
-// compare-exchange): 10^8 keys 943 -> 680 us; 33,554,467 pairs 674 -> 292 us.
+// compare-exchange): 10^8 keys 943 -> 622 us; 33,554,467 pairs 674 -> 292 us.
 template <int EM, uint32_t TOUT, int W, bool PAIRS>
 __global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge64(Phase64 ph, Bufs64 b, RoundArgs ra,
                                                                       const uint32_t* __restrict__ table,
