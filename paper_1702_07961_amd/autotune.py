@@ -1,13 +1,17 @@
 """Autotuner of the sort's run-time parameters (§6.2 tunes the fan-out K and
 the number of workers per platform; here per size bucket on this GPU).
 
-For every size bucket n = 2^b it times the plain keys-only sort of n uniform
-uint32 keys under each candidate (fan-out K, merge output tile, merge kernel
-shape) with HIP events and keeps the fastest; with those fixed it then times
-each base-case shape (keys per lane x waves, and with it the base tile of
-2048, 4096 or 8192 keys).  Key-value sorts get entries of their own: the
-stable sort of n (uint32 key, index) pairs under every fan-out and key-value
-base shape (8 x 4, 8 x 8, 16 x 4).  The table is written as JSON.
+For every size bucket up to n = 2^b it times the plain keys-only sort of n and
+of 3n/4 uniform uint32 keys (a bucket holds sizes on both sides of a round's or
+a wave of workgroups' end) under each candidate (fan-out K, merge output tile,
+merge kernel shape, base-case shape: keys per lane x waves, and with it the base
+tile of 2048, 4096 or 8192 keys) with HIP events, then the fastest few again
+with more repetitions, and keeps the one with the smallest sum.  All shapes are
+tried with all others: chosen one after the other, the merge shape fits a base
+tile that is then not taken (2^20 keys 66 us, 61.5 together).  Key-value sorts
+get entries of their own: the stable sort of (uint32 key, index) pairs under
+every fan-out and key-value base shape (8 x 4, 8 x 8, 16 x 4).
+The table is written as JSON.
 The package loads that table into the library (mms_set_tuning) the first
 time the library is used.
 
@@ -47,6 +51,11 @@ def candidates(log2n: int):
                 yield K, T, v
 
 
+def sizes(n: int):
+    """The sizes timed for the bucket up to n."""
+    return (n, max(1, 3 * n // 4))
+
+
 def time_sort(mms, torch, x, out, ws, reps: int) -> float:
     stream = torch.cuda.current_stream()
     mms.sort(x, out=out, i32=False, workspace=ws)
@@ -81,15 +90,15 @@ def tune_pairs(mms, torch, x_all, min_log2: int, max_log2: int, reps: int, log=p
     for b in range(min_log2, max_log2 + 1):
         n = 1 << b
         x, v, ok, ov = x_all[:n], v_all[:n], ok_all[:n], ov_all[:n]
-        best = None
+        found = []
         for K in FANOUTS:
             for base in PAIR_BASES + PAIR_BASES_16:
                 mms.set_tuning([(64, K, 3840, 0, base, MMS_PAIRS)])
                 ws = torch.empty(max(mms.workspace_bytes(n, pairs=True), 256), dtype=torch.uint8, device="cuda")
-                ms = time_pairs(mms, torch, x, v, ok, ov, ws, max(reps, int(2e6 // n)))
-                if best is None or ms < best[0]:
-                    best = (ms, K, base)
-        ms, K, base = best
+                t = [time_pairs(mms, torch, x[:m], v[:m], ok[:m], ov[:m], ws, max(2 * reps, int(2e6 // n)))
+                     for m in sizes(n)]
+                found.append((sum(t), t[0], K, base))
+        _, ms, K, base = min(found)
         mms.set_tuning([(64, K, 3840, 0, base, MMS_PAIRS)])
         ws = torch.empty(max(mms.workspace_bytes(n, pairs=True), 256), dtype=torch.uint8, device="cuda")
         mms.sort_pairs(x, v, out_keys=ok, out_values=ov, i32=False, workspace=ws)
@@ -118,23 +127,16 @@ def tune(min_log2: int = 8, max_log2: int = 27, reps: int = 5, log=print, keys_f
     for b in range(min_log2, max_log2 + 1) if not keys_from else ():
         n = 1 << b
         x, out = x_all[:n], out_all[:n]
-        best = None
-        for K, T, v in candidates(b):
-            mms.set_tuning([(64, K, T, v)])
-            ws_bytes = mms.workspace_bytes(n)
-            ws = torch.empty(max(ws_bytes, 256), dtype=torch.uint8, device="cuda")
-            r = max(reps, int(2e6 // n))
-            ms = time_sort(mms, torch, x, out, ws, r)
-            if best is None or ms < best[0]:
-                best = (ms, K, T, v)
-        ms, K, T, v = best
-        base = BASES[0]
-        for bs in BASES[1:]:
-            mms.set_tuning([(64, K, T, v, bs)])
+
+        def total(c, r):
+            mms.set_tuning([(64, *c)])
             ws = torch.empty(max(mms.workspace_bytes(n), 256), dtype=torch.uint8, device="cuda")
-            ms_b = time_sort(mms, torch, x, out, ws, max(reps, int(2e6 // n)))
-            if ms_b < ms:
-                ms, base = ms_b, bs
+            t = [time_sort(mms, torch, x[:m], out[:m], ws, r) for m in sizes(n)]
+            return sum(t), t[0], c
+
+        quick = max(2, int(2e5 // n))
+        found = sorted(total((*c, bs), quick) for c in candidates(b) for bs in BASES)
+        _, ms, (K, T, v, base) = min(total(c, max(2 * reps, int(4e6 // n))) for _, _, c in found[:12])
         # the fastest candidate must still sort
         mms.set_tuning([(64, K, T, v, base)])
         ws = torch.empty(max(mms.workspace_bytes(n), 256), dtype=torch.uint8, device="cuda")
@@ -150,8 +152,9 @@ def tune(min_log2: int = 8, max_log2: int = 27, reps: int = 5, log=print, keys_f
     props = torch.cuda.get_device_properties(0)
     return {"device": props.name, "gcn_arch": getattr(props, "gcnArchName", ""),
             "cus": props.multi_processor_count, "created": time.strftime("%Y-%m-%d %H:%M:%S"),
-            "method": "plain sort of 2^b uniform uint32 keys (entries) and stable sort of 2^b "
-                      "(uint32 key, index) pairs (pairs_entries), HIP-event mean over reps",
+            "method": "plain sort of 2^b and 3/4 2^b uniform uint32 keys (entries) and stable sort of as many "
+                      "(uint32 key, index) pairs (pairs_entries), smallest sum of HIP-event means over "
+                      "reps; ms: at 2^b",
             "entries": entries, "pairs_entries": pairs_entries}
 
 
