@@ -1,16 +1,17 @@
 // Sorting 64-bit keys by 64-bit words that cannot hold them (§6.3 also sorts
 // 8-byte integers).
 //
-// A word (mms_device_kt.h) has 52 bits for an element's order, and an
-// element's slot in its tile takes 12 of them.  The words of a tile hold the
-// leading 40 bits of (key - kmin), kmin and kmax being the tile's smallest and
-// largest key: all of them where the range is below 2^40, else keys that agree
-// in those bits (that share a prefix) may differ below.  The tile is sorted by
-// words, and the sorted slots are checked against the keys.  Keys of uniform
-// tiles share prefixes about once in 10^5 tiles; a tile that the words did not
+// A word is a positive normal double: as integers 2^52 (the smallest) to the
+// sentinel, 62 bits for an element's order, of which its slot in its tile takes
+// 12.  The words of a tile hold the leading 50 bits of (key - kmin), kmin and
+// kmax being the tile's smallest and largest key: all of them where the range is
+// below 2^50 (a merge of keys alone then takes them from the words), else keys
+// that agree in those bits (that share a prefix) may differ below.  The tile is
+// sorted by words, and the sorted slots are checked against the keys.  Keys of uniform
+// tiles share prefixes about once in 10^8 tiles; a tile that the words did not
 // put in order is sorted once more, by words that are exact:
-//   bits 47..36  the prefix's rank among the tile's prefixes
-//   bits 35..12  the key's bits below the prefix (24 at most)
+//   bits 37..26  the prefix's rank among the tile's prefixes
+//   bits 25..12  the key's bits below the prefix (14 at most)
 //   bits 11..0   the slot
 // So a tile is sorted at most twice, whatever its keys.
 #pragma once
@@ -25,14 +26,19 @@
 
 namespace mms {
 
-constexpr uint32_t kSlotBits = 12, kPrefixBits = 52u - kSlotBits;
+constexpr uint32_t kSlotBits = 12, kPrefixBits = 62u - kSlotBits;
+
+constexpr uint32_t kWordBase = 1u << 20;   // the smallest normal double's high half
 
 __device__ __forceinline__ uint32_t prefix_shift(uint64_t range) {
     return range >> kPrefixBits ? 64u - kPrefixBits - (uint32_t)__builtin_clzll(range) : 0u;
 }
 __device__ __forceinline__ double order_word(uint64_t order, uint32_t slot) {
-    const uint64_t mant = (order << kSlotBits) | slot;
-    return kt_join(kKtExp | (uint32_t)(mant >> 32), (uint32_t)mant);
+    const uint64_t bits = (order << kSlotBits) | slot;
+    return kt_join((uint32_t)(bits >> 32) + kWordBase, (uint32_t)bits);
+}
+__device__ __forceinline__ uint64_t word_order(double w) {
+    return ((uint64_t)(kt_hi(w) - kWordBase) << 32 | kt_lo(w)) >> kSlotBits;
 }
 __device__ __forceinline__ uint32_t word_slot(double w) { return kt_lo(w) & ((1u << kSlotBits) - 1u); }
 
