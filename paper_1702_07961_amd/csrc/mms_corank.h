@@ -140,23 +140,41 @@ __device__ uint32_t corank_rounds(const KeyT* __restrict__ keys, uint64_t gb, ui
         } else {
             // c precedes this lane's key if c < key, or c <= key for the lanes
             // after its own: the borrow of c - key - [lane > m], which a third
-            // instruction adds to the rank
+            // instruction adds to the rank.  On gfx950 a VALU instruction may
+            // read an SGPR that another one wrote only two wait states later, and
+            // the compiler does not look for that inside inline assembly: four
+            // candidates go through the three steps together, each with carries
+            // of its own, so three instructions lie between.  10^6 keys 106.4 ->
+            // 95.1 us, 10^8 3757 -> 3708, against one candidate after the other
+            // through VCC (which broke the rule).
             const uint32_t klo = (uint32_t)comp, khi = (uint32_t)(comp >> 32);
             uint64_t after = ~1ull;   // lanes after candidate m's
 #pragma unroll 2
             for (uint32_t m = 0; m < total; m += 8) {
 #pragma unroll
-                for (uint32_t e = 0; e < 8; ++e) {
-                    const uint64_t c = sh->comp[m + e];
-                    uint32_t t;
-                    asm("s_mov_b64 vcc, %4\n\t"
-                        "v_subb_co_u32 %1, vcc, %2, %5, vcc\n\t"
-                        "v_subb_co_u32 %1, vcc, %3, %6, vcc\n\t"
-                        "v_addc_co_u32 %0, vcc, 0, %0, vcc"
-                        : "+v"(rank), "=&v"(t)
-                        : "v"((uint32_t)c), "v"((uint32_t)(c >> 32)), "s"(after), "v"(klo), "v"(khi)
-                        : "vcc");
-                    after <<= 1;
+                for (uint32_t e = 0; e < 8; e += 4) {
+                    const uint64_t c0 = sh->comp[m + e], c1 = sh->comp[m + e + 1];
+                    const uint64_t c2 = sh->comp[m + e + 2], c3 = sh->comp[m + e + 3];
+                    uint64_t b0 = after, b1 = after << 1, b2 = after << 2, b3 = after << 3;
+                    uint32_t t0, t1, t2, t3;
+                    asm("v_subb_co_u32_e64 %1, %5, %9, %17, %5\n\t"
+                        "v_subb_co_u32_e64 %2, %6, %11, %17, %6\n\t"
+                        "v_subb_co_u32_e64 %3, %7, %13, %17, %7\n\t"
+                        "v_subb_co_u32_e64 %4, %8, %15, %17, %8\n\t"
+                        "v_subb_co_u32_e64 %1, %5, %10, %18, %5\n\t"
+                        "v_subb_co_u32_e64 %2, %6, %12, %18, %6\n\t"
+                        "v_subb_co_u32_e64 %3, %7, %14, %18, %7\n\t"
+                        "v_subb_co_u32_e64 %4, %8, %16, %18, %8\n\t"
+                        "v_addc_co_u32_e64 %0, %5, 0, %0, %5\n\t"
+                        "v_addc_co_u32_e64 %0, %6, 0, %0, %6\n\t"
+                        "v_addc_co_u32_e64 %0, %7, 0, %0, %7\n\t"
+                        "v_addc_co_u32_e64 %0, %8, 0, %0, %8"
+                        : "+v"(rank), "=&v"(t0), "=&v"(t1), "=&v"(t2), "=&v"(t3), "+&s"(b0), "+&s"(b1), "+&s"(b2),
+                          "+&s"(b3)
+                        : "v"((uint32_t)c0), "v"((uint32_t)(c0 >> 32)), "v"((uint32_t)c1), "v"((uint32_t)(c1 >> 32)),
+                          "v"((uint32_t)c2), "v"((uint32_t)(c2 >> 32)), "v"((uint32_t)c3), "v"((uint32_t)(c3 >> 32)),
+                          "v"(klo), "v"(khi));
+                    after <<= 4;
                 }
             }
         }
