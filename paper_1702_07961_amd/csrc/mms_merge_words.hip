@@ -312,15 +312,21 @@ __global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge64(Phase64 ph
     const uint32_t glast = (uint32_t)glen - 2u;   // a group of two runs or more holds more than a base tile
     uint32_t shift = 0;
     constexpr uint32_t U = 32 / W;                // steps a wave has in flight
+    // Every wave takes the tile's smallest and largest key, whether it has a load
+    // step or not (the last tile of a group may have fewer than waves): the
+    // barriers further down stand in branches on shift, which all waves of the
+    // workgroup must take alike.
+    auto bounds = [&] {
+        // row 0 holds the pieces
+        kmax = lane_u64(row_extreme<true>(kmax), 0);
+        kmin = lane_u64(row_extreme<false>(kmin), 0);
+        shift = prefix_shift(kmax - kmin);
+    };
+    if ((uint32_t)wave >= st.total) bounds();
     load_u64<U, W>(
         src_k + gb, glast, st, wave, lane,
         [&](uint32_t e0) {
-            if (e0 == (uint32_t)wave) {
-                // row 0 holds the pieces
-                kmax = lane_u64(row_extreme<true>(kmax), 0);
-                kmin = lane_u64(row_extreme<false>(kmin), 0);
-                shift = prefix_shift(kmax - kmin);
-            }
+            if (e0 == (uint32_t)wave) bounds();
             if (e0 == 0u) {   // wave 0 plans the levels while its first loads are in flight
                 if ((uint32_t)lane < Kg) {
                     sm.sbeg[lane] = pc.sb;
