@@ -9,9 +9,10 @@
 // (mms_word_merge.h).  After the last level's reads the values take the words'
 // place in LDS, and each is gathered by its word's tag as the keys are stored.
 //
-// 64-bit keys do not fit a word with their slot, so a tile's words hold the
-// leading 50 bits of its keys' range, and a tile that this did not put in
-// order is set right afterwards (k_merge64 below).
+// A word holds 64-bit keys alone whole where a tile's keys span less than 2^62.
+// With their slot they do not fit, so the words of pairs (and of keys that span
+// more) hold the leading 50 bits of the tile's range, and a tile that this did
+// not put in order is set right afterwards (k_merge64 below).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -197,11 +198,13 @@ __global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge_pairs(Phase 
 // ===========================================================================
 // 64-bit keys, alone or with 64-bit values.
 //
-// The words hold as much of the keys as fits (mms_order64.h); words are unique
-// and each piece's are in order, so the merge is exact in the order of the
-// words.  The keys then come back into the words' place, to be checked and
-// gathered.  A tile that is not in order merges its second words: a piece's are
-// in order too, so its levels and items are the same.
+// Keys alone need no slots: where a tile spans less than 2^62 its words are the
+// keys, and they are stored from the words.  Otherwise the words hold as much of
+// the keys as fits with a slot (mms_order64.h); such words are unique and each
+// piece's are in order, so the merge is exact in the order of the words.  The
+// keys then come back into the words' place, to be checked and gathered.  A tile
+// that is not in order merges its second words: a piece's are in order too, so
+// its levels and items are the same.
 // ===========================================================================
 typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
 typedef uint64_t u64x2a8 __attribute__((ext_vector_type(2), aligned(8)));
@@ -311,6 +314,12 @@ __global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge64(Phase64 ph
     }
     const uint32_t glast = (uint32_t)glen - 2u;   // a group of two runs or more holds more than a base tile
     uint32_t shift = 0;
+    // Keys alone that span less than 2^62: the words are the keys.  With slots, keys
+    // of few ids and a small counter below them shared words in every round but the
+    // last and were merged twice: 2*10^7 such keys (three to an id) 1208 -> 788 us,
+    // 10^8 4979 -> 3562; uniform keys, checked and gathered then, 784 -> 724 and
+    // 3696 -> 3481.
+    bool direct = false;
     constexpr uint32_t U = 32 / W;                // steps a wave has in flight
     // Every wave takes the tile's smallest and largest key, whether it has a load
     // step or not (the last tile of a group may have fewer than waves): the
@@ -321,6 +330,7 @@ __global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge64(Phase64 ph
         kmax = lane_u64(row_extreme<true>(kmax), 0);
         kmin = lane_u64(row_extreme<false>(kmin), 0);
         shift = prefix_shift(kmax - kmin);
+        direct = !PAIRS && (kmax - kmin) >> kKeyBits == 0u;
     };
     if ((uint32_t)wave >= st.total) bounds();
     load_u64<U, W>(
@@ -344,8 +354,14 @@ __global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge64(Phase64 ph
             }
         },
         [&](uint32_t slot, int left, uint64_t k0, uint64_t k1) {
-            const double w0 = left > 0 ? order_word((k0 - kmin) >> shift, slot) : kt_sentinel();
-            const double w1 = left > 1 ? order_word((k1 - kmin) >> shift, slot + 1u) : kt_sentinel();
+            double w0, w1;
+            if (direct) {
+                w0 = left > 0 ? key_word(k0 - kmin) : kt_sentinel();
+                w1 = left > 1 ? key_word(k1 - kmin) : kt_sentinel();
+            } else {
+                w0 = left > 0 ? order_word((k0 - kmin) >> shift, slot) : kt_sentinel();
+                w1 = left > 1 ? order_word((k1 - kmin) >> shift, slot + 1u) : kt_sentinel();
+            }
             *reinterpret_cast<d2*>(X + slot) = d2{w0, w1};
         });
     lds_barrier();
@@ -356,9 +372,6 @@ __global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge64(Phase64 ph
     auto store_lds = [&](uint32_t slot, int left, uint64_t a, uint64_t z) {
         if (left > 0) *reinterpret_cast<u64x2*>(E + slot) = u64x2{a, z};
     };
-    // pairs come back for their values in any case, and store their keys the same
-    // way (33,554,432 pairs of 16 keys: 1510 us, from the words 1554)
-    const bool direct = !PAIRS && shift == 0u;
     for (bool exact = false;;) {
         double m[EM];
         WordRow o;
@@ -368,14 +381,13 @@ __global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge64(Phase64 ph
             word_put_lds(X, o, m, lane);
             lds_barrier();
         }
-        // the words hold all of the keys: 10^8 uniform keys (the last round) 3804 ->
-        // 3759 us, nearly sorted ones (every round) 3548 -> 3425; left by `break`,
-        // as a return here moves spills into the levels (4190)
+        // left by `break`, as a return here moves spills into the levels (10^8 keys
+        // 3759 -> 4190 us)
         if (direct) {
             gu64* g = gptr64(dst_k) + obase;
             word_row_put(o, m, lane, [&](int c, int step, double a, double z) {
                 const uint32_t at = 2u * (uint32_t)(c + step);
-                const uint64_t ka = (word_order(a) + kmin) ^ flip_out, kz = (word_order(z) + kmin) ^ flip_out;
+                const uint64_t ka = (word_key(a) + kmin) ^ flip_out, kz = (word_key(z) + kmin) ^ flip_out;
                 if (at + 2u <= cnt) *reinterpret_cast<gu64x2a8*>(g + at) = u64x2{ka, kz};
                 else if (at < cnt) g[at] = ka;
             });

@@ -2,14 +2,15 @@
 // 8-byte integers).
 //
 // A word is a positive normal double: as integers 2^52 (the smallest) to the
-// sentinel, 62 bits for an element's order, of which its slot in its tile takes
-// 12.  The words of a tile hold the leading 50 bits of (key - kmin), kmin and
-// kmax being the tile's smallest and largest key: all of them where the range is
-// below 2^50 (a merge of keys alone then takes them from the words), else keys
-// that agree in those bits (that share a prefix) may differ below.  The tile is
-// sorted by words, and the sorted slots are checked against the keys.  Keys of uniform
-// tiles share prefixes about once in 10^8 tiles; a tile that the words did not
-// put in order is sorted once more, by words that are exact:
+// sentinel, 62 bits for an element's order.  A merge of keys alone whose range is
+// below 2^62 has (key - kmin) for its words, kmin and kmax being the tile's
+// smallest and largest key.  Otherwise an element's slot in its tile takes 12 of
+// the bits, and the words hold the leading 50 of (key - kmin): all of them where
+// the range is below 2^50, else keys that agree in those bits (that share a
+// prefix) may differ below.  The tile is sorted by words, and the sorted slots
+// are checked against the keys.  Keys of uniform tiles share prefixes about once
+// in 10^8 tiles; a tile that the words did not put in order is sorted once more,
+// by words that are exact:
 //   bits 37..26  the prefix's rank among the tile's prefixes
 //   bits 25..12  the key's bits below the prefix (14 at most)
 //   bits 11..0   the slot
@@ -26,7 +27,7 @@
 
 namespace mms {
 
-constexpr uint32_t kSlotBits = 12, kPrefixBits = 62u - kSlotBits;
+constexpr uint32_t kKeyBits = 62, kSlotBits = 12, kPrefixBits = kKeyBits - kSlotBits;
 
 constexpr uint32_t kWordBase = 1u << 20;   // the smallest normal double's high half
 
@@ -37,9 +38,12 @@ __device__ __forceinline__ double order_word(uint64_t order, uint32_t slot) {
     const uint64_t bits = (order << kSlotBits) | slot;
     return kt_join((uint32_t)(bits >> 32) + kWordBase, (uint32_t)bits);
 }
-__device__ __forceinline__ uint64_t word_order(double w) {
-    return ((uint64_t)(kt_hi(w) - kWordBase) << 32 | kt_lo(w)) >> kSlotBits;
+// Words without slots, of which equal ones are equal keys: all 62 bits are the
+// key's.
+__device__ __forceinline__ double key_word(uint64_t offset) {
+    return kt_join((uint32_t)(offset >> 32) + kWordBase, (uint32_t)offset);
 }
+__device__ __forceinline__ uint64_t word_key(double w) { return (uint64_t)(kt_hi(w) - kWordBase) << 32 | kt_lo(w); }
 __device__ __forceinline__ uint32_t word_slot(double w) { return kt_lo(w) & ((1u << kSlotBits) - 1u); }
 
 // Minimum (or maximum) over the 16 lanes of each row.
