@@ -7,10 +7,11 @@
 // smallest and largest key.  Otherwise an element's slot in its tile takes 12 of
 // the bits, and the words hold the leading 50 of (key - kmin): all of them where
 // the range is below 2^50, else keys that agree in those bits (that share a
-// prefix) may differ below.  The tile is sorted by words, and the sorted slots
-// are checked against the keys.  Keys of uniform tiles share prefixes about once
-// in 10^8 tiles; a tile that the words did not put in order is sorted once more,
-// by words that are exact:
+// prefix) may differ below.  (A base tile first leaves out a run of bits that are
+// zero in all of its keys, if the rest then fits.)  The tile is sorted by words,
+// and the sorted slots are checked against the keys.  Keys of uniform tiles share
+// prefixes about once in 10^8 tiles; a tile that the words did not put in order
+// is sorted once more, by words that are exact:
 //   bits 37..26  the prefix's rank among the tile's prefixes
 //   bits 25..12  the key's bits below the prefix (14 at most)
 //   bits 11..0   the slot
@@ -46,14 +47,14 @@ __device__ __forceinline__ double key_word(uint64_t offset) {
 __device__ __forceinline__ uint64_t word_key(double w) { return (uint64_t)(kt_hi(w) - kWordBase) << 32 | kt_lo(w); }
 __device__ __forceinline__ uint32_t word_slot(double w) { return kt_lo(w) & ((1u << kSlotBits) - 1u); }
 
-// Minimum (or maximum) over the 16 lanes of each row.
-template <bool MAX>
-__device__ __forceinline__ uint64_t row_extreme(uint64_t x) {
+// op over the 16 lanes of each row (op(x, x) == x).
+template <class Op>
+__device__ __forceinline__ uint64_t row_reduce(uint64_t x, const Op& op) {
     auto step = [&](auto ctrl) {
         const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)x, decltype(ctrl)::value, 0xF, 0xF, false);
         const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(x >> 32), decltype(ctrl)::value, 0xF, 0xF, false);
         const uint64_t o = ((uint64_t)hi << 32) | lo;
-        x = MAX ? max(x, o) : min(x, o);
+        x = op(x, o);
     };
     step(std::integral_constant<int, 0x121>{});   // row_ror:1
     step(std::integral_constant<int, 0x122>{});
@@ -61,9 +62,41 @@ __device__ __forceinline__ uint64_t row_extreme(uint64_t x) {
     step(std::integral_constant<int, 0x128>{});
     return x;
 }
+template <bool MAX>
+__device__ __forceinline__ uint64_t row_extreme(uint64_t x) {
+    return row_reduce(x, [](uint64_t a, uint64_t b) { return MAX ? max(a, b) : min(a, b); });
+}
 __device__ __forceinline__ uint64_t lane_u64(uint64_t x, int lane) {
     return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), lane) << 32) |
            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane);
+}
+
+// Keys with a run of bits that are zero in all of them (an id in the high half
+// and a counter in the low bits): what is left may fit the 50 bits though the
+// range does not.  ones: the OR of the keys; shift: prefix_shift(kmax - kmin), not
+// zero.
+struct KeyGap {
+    uint32_t low, high;   // bits low .. high - 1 are left out
+    uint64_t first;       // kmin >> high
+    bool fits;
+};
+__device__ __forceinline__ KeyGap key_gap(uint64_t ones, uint64_t kmin, uint64_t kmax, uint32_t shift) {
+    uint64_t runs = ~ones;   // where `have` zeros in a row start
+    if ((uint32_t)__popcll(runs) < shift) return {0u, 0u, 0ull, false};   // as of uniform keys, at once
+    for (uint32_t have = 1; have < shift;) {
+        const uint32_t more = min(have, shift - have);
+        runs &= runs >> more;
+        have += more;
+    }
+    const uint32_t low = runs ? (uint32_t)__builtin_ctzll(runs) : 0u;
+    const uint64_t above = runs ? ones >> low : 0ull;
+    if (!above) return {0u, 0u, 0ull, false};
+    const uint32_t high = low + (uint32_t)__builtin_ctzll(above);
+    const uint64_t first = kmin >> high, span = (kmax >> high) - first;
+    return {low, high, first, low <= kPrefixBits && span >> (kPrefixBits - low) == 0u};
+}
+__device__ __forceinline__ uint64_t without_gap(uint64_t key, const KeyGap& g) {
+    return (((key >> g.high) - g.first) << g.low) | (key & ((1ull << g.low) - 1ull));
 }
 
 // LDS of the check and of the second words, for W waves.
