@@ -53,9 +53,12 @@ def workspace_bytes(n: int, pairs: bool = False, keys64: bool = False) -> int:
     return int(_lib.lib().mms_workspace_bytes(int(n), flags))
 
 
+_ONE_TILE = 2048   # the smallest base tile: a sort that it holds has no merge round and needs no workspace
+
+
 def _workspace(n, pairs, device, workspace, keys64=False):
     torch = _torch()
-    need = workspace_bytes(n, pairs, keys64)
+    need = workspace_bytes(n, pairs, keys64) if n > _ONE_TILE else 0
     if workspace is not None:
         if workspace.numel() * workspace.element_size() < need:
             raise ValueError(f"workspace needs {need} bytes")

@@ -118,7 +118,7 @@ bool valid_tune(uint32_t K, uint32_t Tout, int variant, int base) {
 // takes the first with ceil(log2 n) <= max_log2_n, else the last.  Key-value
 // sorts use the keys-only entries when the table has none of their own.
 Tune tune_for(uint64_t n, bool pairs) {
-    Tune t = env_default();
+    Tune t{};
     {
         std::lock_guard<std::mutex> g(g_tune_mu);
         const uint32_t want = pairs ? MMS_PAIRS : 0u;
@@ -132,7 +132,7 @@ Tune tune_for(uint64_t n, bool pairs) {
             e = &x;
             if (l <= x.max_log2_n) break;
         }
-        if (e) t = Tune{e->fanout, e->merge_tile, (int)e->variant, (int)e->base};
+        t = e ? Tune{e->fanout, e->merge_tile, (int)e->variant, (int)e->base} : env_default();
     }
     if (!valid_tune(t.K, t.Tout, t.variant, t.base)) t = Tune{mms::kMaxFanout, mms::kToutKeys, 0, 0};
     if (pairs) {
