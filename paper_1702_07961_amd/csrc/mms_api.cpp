@@ -151,14 +151,18 @@ Tune tune_for(uint64_t n, bool pairs) {
 // one pass, if one does (a tile's waves and merge steps of sentinels are left
 // out, so the shorter segments lose little: 4096 segments of 2^6 to 2^12 keys
 // 89.9 us in 2048-key tiles and a merge round, 72.8 in 4096-key ones; pairs
-// 157.9 and 95.9; 3000 of 2^8 to 2^13 keys 105.8 and, in 8192-key ones, 84.5);
-// else it stays within the mean segment or at 2048.
+// 157.9 and 95.9; 3000 of 2^8 to 2^13 keys 105.8 and, in 8192-key ones, 84.5)
+// and its launch stays below 2^32 threads (256 or 512 a segment); else it stays
+// within the mean segment or at 2048.
 Tune tune_for_batch(uint64_t total, uint64_t ns, uint64_t maxn, bool pairs) {
     Tune t = tune_for(std::max<uint64_t>(total, 1), pairs);
     const uint64_t mean = ns ? total / ns : total;
-    if (maxn <= mms::base_tile(2)) t.base = 2;
-    else if (maxn <= mms::base_tile(5)) t.base = 5;
-    else if (!pairs && maxn <= mms::base_tile(6)) t.base = 6;
+    auto one_pass = [&](int base) {
+        return maxn <= mms::base_tile(base) && ns * 64u * (uint64_t)mms::base_w(base) < (1ull << 32);
+    };
+    if (one_pass(2)) t.base = 2;
+    else if (one_pass(5)) t.base = 5;
+    else if (!pairs && one_pass(6)) t.base = 6;
     else if (mms::base_tile(t.base) > std::max<uint64_t>(mms::kT1, mean)) t.base = 2;
     return t;
 }

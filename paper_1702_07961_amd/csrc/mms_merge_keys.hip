@@ -176,8 +176,10 @@ hipError_t launch_merge_keys(const Phase& ph, const Bufs& b, const RoundArgs& ra
     if (ph.tiles == 0) return hipSuccess;
     if (variant == 4) return launch_merge_heap(ph, b, ra, table, flip, s);
     // a pass of rows holds any pair: eight waves of 256-key blocks up to
-    // 7680-key tiles, of 128-key ones up to 3584, sixteen up to 7424
-    if (variant == 1 && ra.Tout <= 7424) return launch_variant<8, 16, 7424, 8>(ph, b, ra, table, flip, s);
+    // 7680-key tiles, of 128-key ones up to 3584, sixteen up to 7424 (a launch has
+    // less than 2^32 threads: 2^32 - 1 keys in 1024-key tiles take eight waves)
+    if (variant == 1 && ra.Tout <= 7424 && ph.tiles < 1u << 22)
+        return launch_variant<8, 16, 7424, 8>(ph, b, ra, table, flip, s);
     if (variant == 2 && ra.Tout <= 3584) return launch_variant<8, 8, 3584, 8>(ph, b, ra, table, flip, s);
     if (ra.Tout <= 7680) return launch_variant<16, 8, 7680, 8>(ph, b, ra, table, flip, s);
     return launch_variant<16, 16, kToutKeys, 8>(ph, b, ra, table, flip, s);
