@@ -147,7 +147,7 @@ def bench_batched(mms, torch, np, mmsgen, reps: int = 5) -> dict:
     out = torch.empty_like(x)
     ws = torch.empty(mms.segmented_workspace_bytes(off), dtype=torch.uint8, device="cuda")
     stream = torch.cuda.current_stream()
-    mms.segmented_sort(x, off, out_keys=out, workspace=ws, i32=False)     # captures the graph
+    mms.segmented_sort(x, off, out_keys=out, workspace=ws, i32=False)     # plans the batch
     torch.cuda.synchronize()
     a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     a.record(stream)

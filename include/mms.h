@@ -195,9 +195,6 @@ int mms_copy_u32(const uint32_t* d_in, uint32_t* d_out, uint64_t n, void* stream
  * every segment's tiles (the base case, then per round the partition and
  * the merge).  The first call with a given (offsets, pointers, flags,
  * tuning) plans it, and later calls with the same signature reuse the plan.
- * With MMS_GRAPH=1 in the environment the launches are also captured into a
- * hipGraph and replayed with a single graph launch on `stream`, which takes
- * more host time than launching them.
  *
  * Memory: all device memory is the caller's.  The workspace holds the
  * ping-pong buffers, the partition table and the batch metadata (a 64-byte
@@ -208,7 +205,7 @@ int mms_copy_u32(const uint32_t* d_in, uint32_t* d_out, uint64_t n, void* stream
  * launches, so the workspace may be used for anything else between calls.
  * An evicted signature is torn down only after its last launch completes.
  * Errors: MMS_EINVAL (offsets decreasing, buffers, workspace), MMS_ENOMEM
- * (pinned staging of the metadata), MMS_EHIP (capture, copy or launch).
+ * (pinned staging of the metadata), MMS_EHIP (copy or launch).
  */
 size_t mms_segmented_workspace_bytes(const uint64_t* h_offsets, uint64_t num_segs, uint32_t flags);
 int mms_segmented_sort(const uint32_t* d_kin, uint32_t* d_kout, const uint32_t* d_vin, uint32_t* d_vout,

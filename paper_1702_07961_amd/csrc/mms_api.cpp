@@ -1,6 +1,6 @@
 // Host runtime of libmms: plans, workspace layout, argument checks, the
 // phase loop (base case, then partition + merge per round), the segmented
-// batch with its hipGraph cache, the tuning table, and the C ABI declared in
+// batch with its cache of plans, the tuning table, and the C ABI declared in
 // include/mms.h.  Kernels are launched only through the launchers of
 // the .hip files.
 #include <hip/hip_runtime.h>
@@ -54,7 +54,7 @@ std::vector<TimingRec> g_recs;
 std::vector<hipEvent_t> g_pool;
 uint64_t g_launch[MMS_KERNEL_KINDS];
 double g_ms[MMS_KERNEL_KINDS];
-thread_local bool g_capturing = false;   // launches are captured into a graph, or timed as one batch
+thread_local bool g_untimed = false;   // the launches of a batch, which are timed as one
 
 hipEvent_t take_event() {
     if (!g_pool.empty()) {
@@ -68,10 +68,10 @@ hipEvent_t take_event() {
 }
 }  // namespace
 
-void set_capturing(bool on) { g_capturing = on; }
+void set_untimed(bool on) { g_untimed = on; }
 
 Timed::Timed(int kind, hipStream_t s) : kind_(kind), s_(s) {
-    if (g_capturing) return;
+    if (g_untimed) return;
     std::lock_guard<std::mutex> g(g_tmu);
     if (!g_timing || !((g_kinds >> kind) & 1u)) return;
     a_ = take_event();
@@ -592,18 +592,14 @@ uint64_t seg_ws_bytes(const uint64_t* off, uint64_t ns, bool pairs, const SegSha
 // A planned batch, keyed by offsets, pointers and tuning: the host image of
 // its metadata in pinned host memory the library owns (uploaded into the
 // caller's workspace by an asynchronous copy on the caller's stream before
-// every launch), and with MMS_GRAPH=1 the instantiated graph of all kernel
-// launches.  The event is recorded after each launch, so an entry is torn down
-// only after the last work that reads its image or runs its graph has
-// finished.  An entry whose launches a caller captured stays: the captured
+// every launch).  The event is recorded after the launches, so an entry is torn
+// down only after the last work that reads its image has finished.  An entry whose launches a caller captured stays: the captured
 // copy reads its image whenever it is replayed.
 struct SegEntry {
     std::string key;
     SegPlan plan;
     void* h_meta = nullptr;
     hipEvent_t last_use = nullptr;
-    hipGraphExec_t exec = nullptr;
-    hipGraph_t graph = nullptr;
     bool captured = false;
 };
 
@@ -616,12 +612,8 @@ void drop_entry(SegEntry& e) {
         (void)hipEventSynchronize(e.last_use);
         (void)hipEventDestroy(e.last_use);
     }
-    if (e.exec) (void)hipGraphExecDestroy(e.exec);
-    if (e.graph) (void)hipGraphDestroy(e.graph);
     if (e.h_meta) (void)hipHostFree(e.h_meta);
     e.last_use = nullptr;
-    e.exec = nullptr;
-    e.graph = nullptr;
     e.h_meta = nullptr;
 }
 
@@ -638,18 +630,9 @@ std::string seg_key(const uint64_t* off, uint64_t ns, uint32_t flags, const void
 }
 
 // A batch is at most 1 + 2 R launches of one to four microseconds of host time
-// each; launched as a graph they take longer (host time a call, graph and
-// launches: 4096 segments of 2^6 to 2^12 keys, one launch, 60 and 35 us; 300 of
-// 2^8 to 2^16, five, 137 and 25 us), so the graph is built on request only.
-bool seg_graph_enabled() {
-    static const bool on = [] {
-        const char* no = getenv("MMS_NO_GRAPH");
-        const char* yes = getenv("MMS_GRAPH");
-        return yes && atoi(yes) != 0 && !(no && atoi(no) != 0);
-    }();
-    return on;
-}
-
+// each.  A hipGraph of them took longer (host time a call, graph and launches:
+// 4096 segments of 2^6 to 2^12 keys, one launch, 60 and 35 us; 300 of 2^8 to
+// 2^16, five, 137 and 25 us).
 int segmented_impl(const uint32_t* kin, uint32_t* kout, const uint32_t* vin, uint32_t* vout, const uint64_t* off,
                    uint64_t ns, void* ws, size_t ws_bytes, uint32_t flags, hipStream_t s) {
     const bool pairs = vin != nullptr;
@@ -737,54 +720,15 @@ int segmented_impl(const uint32_t* kin, uint32_t* kout, const uint32_t* vin, uin
     if (capturing) e.captured = true;
     hipError_t ue = hipMemcpyAsync(d_meta, e.h_meta, p.meta_bytes, hipMemcpyHostToDevice, s);
     if (ue != hipSuccess) return hip_fail(ue, "batch metadata upload");
-    if (capturing || !seg_graph_enabled()) {
-        {
-            Timed tm(MMS_KERNEL_SEGMENTED, s);
-            set_capturing(true);   // timed as one
-            rc = run_batch(p.bt, d_segs, d_tasks, table, flip, s);
-            set_capturing(false);
-        }
-        const hipError_t ee = capturing ? hipSuccess : hipEventRecord(e.last_use, s);
-        if (rc) return rc;
-        return ee == hipSuccess ? MMS_OK : hip_fail(ee, "batch event");
-    }
-
-    if (!e.exec) {
-        hipStream_t cap = nullptr;
-        hipError_t he = hipStreamCreateWithFlags(&cap, hipStreamNonBlocking);
-        if (he != hipSuccess) return hip_fail(he, "capture stream");
-        he = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
-        if (he != hipSuccess) {
-            (void)hipStreamDestroy(cap);
-            return hip_fail(he, "begin capture");
-        }
-        set_capturing(true);
-        rc = run_batch(p.bt, d_segs, d_tasks, table, flip, cap);
-        set_capturing(false);
-        hipGraph_t graph = nullptr;
-        he = hipStreamEndCapture(cap, &graph);
-        (void)hipStreamDestroy(cap);
-        if (rc) {
-            if (graph) (void)hipGraphDestroy(graph);
-            return rc;
-        }
-        if (he != hipSuccess) return hip_fail(he, "end capture");
-        he = hipGraphInstantiate(&e.exec, graph, nullptr, nullptr, 0);
-        if (he != hipSuccess) {
-            (void)hipGraphDestroy(graph);
-            return hip_fail(he, "graph instantiate");
-        }
-        e.graph = graph;
-    }
-    hipError_t he;
     {
         Timed tm(MMS_KERNEL_SEGMENTED, s);
-        he = hipGraphLaunch(e.exec, s);
+        set_untimed(true);   // the launches are timed as one
+        rc = run_batch(p.bt, d_segs, d_tasks, table, flip, s);
+        set_untimed(false);
     }
-    if (he != hipSuccess) return hip_fail(he, "graph launch");
-    he = hipEventRecord(e.last_use, s);
-    if (he != hipSuccess) return hip_fail(he, "batch event");
-    return MMS_OK;
+    const hipError_t ee = capturing ? hipSuccess : hipEventRecord(e.last_use, s);
+    if (rc) return rc;
+    return ee == hipSuccess ? MMS_OK : hip_fail(ee, "batch event");
 }
 
 }  // namespace

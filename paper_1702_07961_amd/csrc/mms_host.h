@@ -19,8 +19,8 @@ int fail(int code, const char* fmt, ...) __attribute__((format(printf, 2, 3)));
 int hip_fail(hipError_t e, const char* what);
 const char* last_error();
 
-// Brackets one kernel launch (or graph launch) with events on its stream
-// while mms_timing is enabled.
+// Brackets a kernel launch, or the launches of a batch, with events on its
+// stream while mms_timing is enabled.
 class Timed {
   public:
     Timed(int kind, hipStream_t s);
@@ -34,8 +34,8 @@ class Timed {
     hipEvent_t a_ = nullptr, b_ = nullptr;
 };
 
-// Launches made on this thread are being captured into a graph (no timing).
-void set_capturing(bool on);
+// Launches made on this thread are not timed one by one (a batch is timed as a whole).
+void set_untimed(bool on);
 
 struct Tune {
     uint32_t K;      // merge fan-out
