@@ -204,6 +204,10 @@ int mms_copy_u32(const uint32_t* d_in, uint32_t* d_out, uint64_t n, void* stream
  * it into the workspace with an asynchronous copy on `stream` ahead of the
  * launches, so the workspace may be used for anything else between calls.
  * An evicted signature is torn down only after its last launch completes.
+ * A call on a stream that the caller is capturing needs no call before it and
+ * touches no kept signature: its image belongs to the captured graph and to
+ * what is instantiated from it, and is freed by a later batch once the last of
+ * them is destroyed.
  * Errors: MMS_EINVAL (offsets decreasing, buffers, workspace), MMS_ENOMEM
  * (pinned staging of the metadata), MMS_EHIP (copy or launch).
  */

@@ -589,18 +589,100 @@ uint64_t seg_ws_bytes(const uint64_t* off, uint64_t ns, bool pairs, const SegSha
            align_up(align_up(sh.count * sizeof(mms::SegDesc)) + ntasks * sizeof(mms::TileTask));
 }
 
-// A planned batch, keyed by offsets, pointers and tuning: the host image of
-// its metadata in pinned host memory the library owns (uploaded into the
-// caller's workspace by an asynchronous copy on the caller's stream before
-// every launch).  The event is recorded after the launches, so an entry is torn
-// down only after the last work that reads its image has finished.  An entry whose launches a caller captured stays: the captured
-// copy reads its image whenever it is replayed.
+// Calls that another thread's or this stream's capture would not allow (pinned
+// memory, events) are made in relaxed mode: they belong to no capture.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    bool on;
+    RelaxedCapture() : on(hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess) {}
+    ~RelaxedCapture() {
+        if (on) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+};
+
+// The host image of a batch's metadata (SegDesc table, then the tasks) in pinned
+// memory that the library owns, uploaded into the caller's workspace by an
+// asynchronous copy on the caller's stream ahead of the launches.
+hipError_t make_image(const SegPlan& p, const uint32_t* kin, uint32_t* kout, const uint32_t* vin, uint32_t* vout,
+                      uint8_t* ws, void** image) {
+    RelaxedCapture relaxed;
+    *image = nullptr;
+    const hipError_t he = hipHostMalloc(image, p.meta_bytes, hipHostMallocDefault);
+    if (he != hipSuccess) return he;
+    uint8_t* img = (uint8_t*)*image;
+    memset(img, 0, p.meta_bytes);
+    uint32_t* ws_k = (uint32_t*)ws;
+    uint32_t* ws_v = p.pairs ? (uint32_t*)(ws + p.off_vals) : nullptr;
+    mms::SegDesc* sd = (mms::SegDesc*)img;
+    for (size_t i = 0; i < p.seg_n.size(); ++i) {
+        const uint64_t o = p.seg_off[i];
+        sd[i] = mms::SegDesc{kin + o, p.pairs ? vin + o : nullptr, kout + o, p.pairs ? vout + o : nullptr,
+                             ws_k + o, p.pairs ? ws_v + o : nullptr, p.seg_n[i], 0};
+    }
+    size_t at = p.seg_bytes;
+    for (auto& v : p.bt.phases) {
+        if (!v.empty()) memcpy(img + at, v.data(), v.size() * sizeof(mms::TileTask));
+        at += v.size() * sizeof(mms::TileTask);
+    }
+    return hipSuccess;
+}
+
+// Images of batches that a caller captured belong to the caller's graph, which
+// reads them at every replay: the graph and what is instantiated from it hold a
+// user object whose destructor hands the image back here.  It may run inside any
+// call of the runtime, so it only notes the image, and the next batch frees it.
+// (Never destroyed: graphs may outlive this library's statics.)
+std::mutex& dead_mu() {
+    static std::mutex* m = new std::mutex;
+    return *m;
+}
+std::vector<void*>& dead_images() {
+    static std::vector<void*>* v = new std::vector<void*>;
+    return *v;
+}
+void hand_back(void* image) {
+    std::lock_guard<std::mutex> g(dead_mu());
+    dead_images().push_back(image);
+}
+void free_dead_images() {
+    std::vector<void*> v;
+    {
+        std::lock_guard<std::mutex> g(dead_mu());
+        v.swap(dead_images());
+    }
+    if (v.empty()) return;
+    RelaxedCapture relaxed;
+    for (void* p : v) (void)hipHostFree(p);
+}
+
+// Give the image to the graph that s is captured into (or back, if that fails).
+hipError_t give_to_graph(void* image, hipStream_t s) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    unsigned long long id = 0;
+    hipGraph_t graph = nullptr;
+    const hipGraphNode_t* deps = nullptr;
+    size_t ndeps = 0;
+    hipUserObject_t owner = nullptr;
+    hipError_t e = hipStreamGetCaptureInfo_v2(s, &cs, &id, &graph, &deps, &ndeps);
+    if (e == hipSuccess && !graph) e = hipErrorStreamCaptureInvalidated;
+    if (e == hipSuccess) e = hipUserObjectCreate(&owner, image, hand_back, 1, hipUserObjectNoDestructorSync);
+    if (e != hipSuccess) {
+        hand_back(image);
+        return e;
+    }
+    e = hipGraphRetainUserObject(graph, owner, 1, hipGraphUserObjectMove);
+    if (e != hipSuccess) (void)hipUserObjectRelease(owner, 1);   // hands the image back
+    return e;
+}
+
+// A planned batch, keyed by offsets, pointers and tuning, with its image.  The
+// event is recorded after the launches, so an entry is torn down only after the
+// last work that reads its image has finished.
 struct SegEntry {
     std::string key;
     SegPlan plan;
     void* h_meta = nullptr;
     hipEvent_t last_use = nullptr;
-    bool captured = false;
 };
 
 std::mutex g_seg_mu;
@@ -608,11 +690,13 @@ std::list<SegEntry> g_seg_cache;   // most recent first
 constexpr size_t kSegCacheMax = 8;
 
 void drop_entry(SegEntry& e) {
+    RelaxedCapture relaxed;
+    bool idle = true;
     if (e.last_use) {
-        (void)hipEventSynchronize(e.last_use);
+        idle = hipEventSynchronize(e.last_use) == hipSuccess;
         (void)hipEventDestroy(e.last_use);
     }
-    if (e.h_meta) (void)hipHostFree(e.h_meta);
+    if (e.h_meta && idle) (void)hipHostFree(e.h_meta);   // not known to be idle: left alone
     e.last_use = nullptr;
     e.h_meta = nullptr;
 }
@@ -644,89 +728,76 @@ int segmented_impl(const uint32_t* kin, uint32_t* kout, const uint32_t* vin, uin
     if (rc) return rc;
     if (sh.count == 0) return MMS_OK;
 
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    (void)hipStreamIsCapturing(s, &cs);
+    const bool capturing = cs == hipStreamCaptureStatusActive;
+    if (!capturing) free_dead_images();
+
     const void* ptrs[5] = {kin, kout, vin, vout, ws};
     const std::string key = seg_key(off, ns, flags | (pairs ? MMS_PAIRS : 0u), ptrs, 5, sh.tune);
     std::lock_guard<std::mutex> lock(g_seg_mu);
     auto it = std::find_if(g_seg_cache.begin(), g_seg_cache.end(), [&](const SegEntry& e) { return e.key == key; });
-    if (it != g_seg_cache.end()) {
-        rc = check_buffers(kin, vin, kout, vout, it->plan.total, ws, it->plan.ws_bytes, ws_bytes);
-        if (rc) return rc;
-    } else {
-        SegPlan sp;
-        make_seg_plan(off, ns, pairs, sh.tune, sp);
-        rc = check_buffers(kin, vin, kout, vout, sp.total, ws, sp.ws_bytes, ws_bytes);
-        if (rc) return rc;
-        SegEntry e;
-        e.key = key;
-        e.plan = std::move(sp);
-        const SegPlan& p = e.plan;
-        uint8_t* wsb = (uint8_t*)ws;
-        uint32_t* ws_k = (uint32_t*)wsb;
-        uint32_t* ws_v = pairs ? (uint32_t*)(wsb + p.off_vals) : nullptr;
-        // host image of the metadata: SegDesc table, then the tasks
-        hipError_t he = hipHostMalloc(&e.h_meta, p.meta_bytes, hipHostMallocDefault);
-        if (he != hipSuccess) {
-            e.h_meta = nullptr;
+    SegPlan sp;
+    if (it == g_seg_cache.end()) make_seg_plan(off, ns, pairs, sh.tune, sp);
+    const SegPlan* p = it == g_seg_cache.end() ? &sp : &it->plan;
+    rc = check_buffers(kin, vin, kout, vout, p->total, ws, p->ws_bytes, ws_bytes);
+    if (rc) return rc;
+
+    void* image = nullptr;
+    hipEvent_t last_use = nullptr;
+    if (capturing) {   // an image of its own, and no entry is touched
+        hipError_t he = make_image(*p, kin, kout, vin, vout, (uint8_t*)ws, &image);
+        if (he != hipSuccess)
             return fail(MMS_ENOMEM, "pinned staging of the batch metadata: %s", hipGetErrorString(he));
-        }
-        he = hipEventCreateWithFlags(&e.last_use, hipEventDisableTiming);
-        if (he != hipSuccess) {
-            e.last_use = nullptr;
-            drop_entry(e);
-            return hip_fail(he, "batch event");
-        }
-        uint8_t* img = (uint8_t*)e.h_meta;
-        memset(img, 0, p.meta_bytes);
-        mms::SegDesc* sd = (mms::SegDesc*)img;
-        for (size_t i = 0; i < p.seg_n.size(); ++i) {
-            const uint64_t o = p.seg_off[i];
-            sd[i] = mms::SegDesc{kin + o, pairs ? vin + o : nullptr, kout + o, pairs ? vout + o : nullptr,
-                                 ws_k + o, pairs ? ws_v + o : nullptr, p.seg_n[i], 0};
-        }
-        size_t at = p.seg_bytes;
-        for (auto& v : p.bt.phases) {
-            if (!v.empty()) memcpy(img + at, v.data(), v.size() * sizeof(mms::TileTask));
-            at += v.size() * sizeof(mms::TileTask);
-        }
-        g_seg_cache.push_front(std::move(e));
-        size_t kept = 0;
-        for (auto i = g_seg_cache.begin(); i != g_seg_cache.end();) {
-            if (i->captured || ++kept <= kSegCacheMax) {
-                ++i;
-            } else {
-                drop_entry(*i);
-                i = g_seg_cache.erase(i);
+        he = give_to_graph(image, s);
+        if (he != hipSuccess) return hip_fail(he, "batch metadata of a capture");
+    } else {
+        if (it == g_seg_cache.end()) {
+            SegEntry e;
+            e.key = key;
+            hipError_t he = make_image(sp, kin, kout, vin, vout, (uint8_t*)ws, &e.h_meta);
+            if (he != hipSuccess)
+                return fail(MMS_ENOMEM, "pinned staging of the batch metadata: %s", hipGetErrorString(he));
+            {
+                RelaxedCapture relaxed;
+                he = hipEventCreateWithFlags(&e.last_use, hipEventDisableTiming);
             }
+            if (he != hipSuccess) {
+                e.last_use = nullptr;
+                drop_entry(e);
+                return hip_fail(he, "batch event");
+            }
+            e.plan = std::move(sp);
+            g_seg_cache.push_front(std::move(e));
+            while (g_seg_cache.size() > kSegCacheMax) {
+                drop_entry(g_seg_cache.back());
+                g_seg_cache.pop_back();
+            }
+        } else if (it != g_seg_cache.begin()) {
+            g_seg_cache.splice(g_seg_cache.begin(), g_seg_cache, it);
         }
-        it = g_seg_cache.begin();
+        const SegEntry& e = g_seg_cache.front();
+        p = &e.plan;
+        image = e.h_meta;
+        last_use = e.last_use;
     }
-    if (it != g_seg_cache.begin()) {
-        g_seg_cache.splice(g_seg_cache.begin(), g_seg_cache, it);
-        it = g_seg_cache.begin();
-    }
-    SegEntry& e = *it;
-    const SegPlan& p = e.plan;
-    uint8_t* d_meta = (uint8_t*)ws + p.off_meta;
+    uint8_t* d_meta = (uint8_t*)ws + p->off_meta;
     const mms::SegDesc* d_segs = (const mms::SegDesc*)d_meta;
-    const mms::TileTask* d_tasks = (const mms::TileTask*)(d_meta + p.seg_bytes);
-    uint32_t* table = (uint32_t*)((uint8_t*)ws + p.off_table);
+    const mms::TileTask* d_tasks = (const mms::TileTask*)(d_meta + p->seg_bytes);
+    uint32_t* table = (uint32_t*)((uint8_t*)ws + p->off_table);
     const uint32_t flip = (flags & MMS_KEY_I32) ? 0x80000000u : 0u;
     // the metadata goes into the caller's workspace on the caller's stream,
     // ahead of the launches that read it (every call: the caller may have
     // used the workspace for something else in between)
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    (void)hipStreamIsCapturing(s, &cs);
-    const bool capturing = cs == hipStreamCaptureStatusActive;
-    if (capturing) e.captured = true;
-    hipError_t ue = hipMemcpyAsync(d_meta, e.h_meta, p.meta_bytes, hipMemcpyHostToDevice, s);
+    const hipError_t ue = hipMemcpyAsync(d_meta, image, p->meta_bytes, hipMemcpyHostToDevice, s);
     if (ue != hipSuccess) return hip_fail(ue, "batch metadata upload");
     {
         Timed tm(MMS_KERNEL_SEGMENTED, s);
         set_untimed(true);   // the launches are timed as one
-        rc = run_batch(p.bt, d_segs, d_tasks, table, flip, s);
+        rc = run_batch(p->bt, d_segs, d_tasks, table, flip, s);
         set_untimed(false);
     }
-    const hipError_t ee = capturing ? hipSuccess : hipEventRecord(e.last_use, s);
+    const hipError_t ee = last_use ? hipEventRecord(last_use, s) : hipSuccess;
     if (rc) return rc;
     return ee == hipSuccess ? MMS_OK : hip_fail(ee, "batch event");
 }
