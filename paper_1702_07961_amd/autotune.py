@@ -5,13 +5,13 @@ For every size bucket up to n = 2^b it times the plain keys-only sort of n and
 of 3n/4 uniform uint32 keys (a bucket holds sizes on both sides of a round's or
 a wave of workgroups' end) under each candidate (fan-out K, merge output tile,
 merge kernel shape, base-case shape: keys per lane x waves, and with it the base
-tile of 2048, 4096 or 8192 keys) with HIP events, then the fastest few again
-with more repetitions, and keeps the one with the smallest sum.  All shapes are
-tried with all others: chosen one after the other, the merge shape fits a base
-tile that is then not taken (2^20 keys 66 us, 61.5 together).  Key-value sorts
-get entries of their own: the stable sort of (uint32 key, index) pairs under
-every fan-out and key-value base shape (8 x 4, 8 x 8, 16 x 4).
-The table is written as JSON.
+tile of 2048, 4096 or 8192 keys) with HIP events (small sorts in a graph, or the
+host's time would be taken), then the fastest few again with more repetitions,
+and keeps the one with the smallest sum.  All shapes are tried with all others:
+chosen one after the other, the merge shape fits a base tile that is then not
+taken (2^20 keys 66 us, 61.5 together).  Key-value sorts get entries of their
+own: the stable sort of (uint32 key, index) pairs under every fan-out and
+key-value base shape (8 x 4, 8 x 8, 16 x 4).  The table is written as JSON.
 The package loads that table into the library (mms_set_tuning) the first
 time the library is used.
 
@@ -51,35 +51,58 @@ def candidates(log2n: int):
                 yield K, T, v
 
 
+def kernel_of(T: int, v: int) -> int:
+    """The variant that names the merge kernel which variant v runs for merge
+    tiles of T (launch_merge_keys): one kernel timed under several names would
+    have that many draws at the smallest time."""
+    if v == 4 or (v == 1 and T <= 7424) or (v == 2 and T <= 3584):
+        return v
+    return 0
+
+
 def sizes(n: int):
     """The sizes timed for the bucket up to n."""
     return (n, max(1, 3 * n // 4))
 
 
-def time_sort(mms, torch, x, out, ws, reps: int) -> float:
-    stream = torch.cuda.current_stream()
-    mms.sort(x, out=out, i32=False, workspace=ws)
+GRAPHED = 1 << 14   # sorts up to this size are timed in a graph: the host takes as long to launch them
+GRAPH_SORTS = 50
+
+
+def time_calls(torch, call, n: int, reps: int) -> float:
+    """Milliseconds a call takes, the calls one after the other."""
+    call()
     torch.cuda.synchronize()
     a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-    a.record(stream)
+    if n <= GRAPHED:
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(GRAPH_SORTS):
+                call()
+        graph.replay()
+        best = float("inf")
+        for _ in range(max(3, min(reps // GRAPH_SORTS, 20))):
+            a.record()
+            graph.replay()
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) / GRAPH_SORTS)
+        return best
+    a.record()
     for _ in range(reps):
-        mms.sort(x, out=out, i32=False, workspace=ws)
-    b.record(stream)
+        call()
+    b.record()
     torch.cuda.synchronize()
     return a.elapsed_time(b) / reps
+
+
+def time_sort(mms, torch, x, out, ws, reps: int) -> float:
+    return time_calls(torch, lambda: mms.sort(x, out=out, i32=False, workspace=ws), x.numel(), reps)
 
 
 def time_pairs(mms, torch, x, v, ok, ov, ws, reps: int) -> float:
-    stream = torch.cuda.current_stream()
-    mms.sort_pairs(x, v, out_keys=ok, out_values=ov, i32=False, workspace=ws)
-    torch.cuda.synchronize()
-    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-    a.record(stream)
-    for _ in range(reps):
-        mms.sort_pairs(x, v, out_keys=ok, out_values=ov, i32=False, workspace=ws)
-    b.record(stream)
-    torch.cuda.synchronize()
-    return a.elapsed_time(b) / reps
+    return time_calls(torch, lambda: mms.sort_pairs(x, v, out_keys=ok, out_values=ov, i32=False, workspace=ws),
+                      x.numel(), reps)
 
 
 def tune_pairs(mms, torch, x_all, min_log2: int, max_log2: int, reps: int, log=print) -> list:
@@ -135,7 +158,7 @@ def tune(min_log2: int = 8, max_log2: int = 27, reps: int = 5, log=print, keys_f
             return sum(t), t[0], c
 
         quick = max(2, int(2e5 // n))
-        found = sorted(total((*c, bs), quick) for c in candidates(b) for bs in BASES)
+        found = sorted(total((*c, bs), quick) for c in candidates(b) if c[2] == kernel_of(c[1], c[2]) for bs in BASES)
         _, ms, (K, T, v, base) = min(total(c, max(2 * reps, int(4e6 // n))) for _, _, c in found[:12])
         # the fastest candidate must still sort
         mms.set_tuning([(64, K, T, v, base)])
