@@ -1,12 +1,12 @@
 // Device building blocks of the multiway mergesort on gfx950 (wave64).
 //
-// Everything here obeys one rule that makes the LDS traffic free of bank
-// conflicts whatever the data: every LDS instruction touches addresses that
-// are a fixed function of (lane, step) plus a wave-uniform base.  All
-// data-dependent routing happens in registers, through compare-exchange
-// networks and cross-lane exchanges (§2.2 and §4.2 of the paper explain why
-// data-dependent shared-memory addressing is what costs the pairwise
-// mergesorts their bank conflicts).
+// Exchanges and changes of layout touch LDS at addresses that are a fixed
+// function of (lane, step) plus a wave-uniform base, and elements are ordered in
+// registers, by compare-exchange networks and cross-lane exchanges (§2.2 and
+// §4.2 of the paper explain why data-dependent shared-memory addressing is what
+// costs the pairwise mergesorts their bank conflicts).  What does depend on the
+// data is where a merge block's rows start in their runs and the gather of
+// values by tag; these conflict, at 9 to 39 % of a kernel's LDS cycles.
 //
 // Element kinds: Elem<false> is a 32-bit key (unsigned order; signed keys
 // are mapped with key ^ 0x80000000 on the way in and back on the way out).

@@ -25,9 +25,11 @@ namespace mms {
 // Base case: the network of mms_tile_net.h on words that hold as much of the
 // keys as fits (mms_order64.h).  A thread keeps its keys in registers: they go
 // where the words were to be checked, and again if the tile is sorted twice.
-// 10^8 keys 1244 -> 688 us against a network of 64-bit keys with an exchange for
+// 10^8 keys 1244 -> 595 us against a network of 64-bit keys with an exchange for
 // every lane and wave distance (8 per lane x 8 waves); 33,554,467 pairs 774 ->
-// 310 us against one of keys and tags (2048-pair tiles).
+// 243 us against one of keys and tags (2048-pair tiles).  A tile that is sorted
+// twice takes longer than that network up to 10^5 elements or so (4000 keys 18.4
+// us, 24.4 here; 10^6 131 and 109).
 // ===========================================================================
 template <int W, bool PAIRS>
 __global__ __launch_bounds__(W * 64, 3) void k_tile_sort_net64(Phase64 ph, Bufs64 b, uint64_t flip) {

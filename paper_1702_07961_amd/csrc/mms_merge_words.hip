@@ -40,9 +40,10 @@ typedef const __attribute__((address_space(1))) u32x2a4 cgu32x2a4;
 // Bound by VALU issue (74 % of the launch's cycles; LDS half of them).  LDS
 // holds one 8-byte word per element and nothing else that grows with the tile,
 // so four workgroups of four waves share a compute unit.  2^27 pairs, K = 16:
-// 0.81 ms per launch on average when it was written (0.72 now), where 512-pair blocks of a wave (two level
-// buffers of keys and tags, the values in LDS throughout, two workgroups of
-// eight waves) took 1.06.  With the values in LDS throughout and all lane
+// 0.72 ms per launch on average (0.81 with items planned pair by pair, branching
+// loads and 8-byte stores), where 512-pair blocks of a wave (two level buffers of
+// keys and tags, the values in LDS throughout, two workgroups of eight waves) took
+// 1.06.  With the values in LDS throughout and all lane
 // distances by DPP, three workgroups fit: 0.92.
 template <int EM, uint32_t TOUT, int W>
 __global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge_pairs(Phase ph, Bufs b, RoundArgs ra,
@@ -243,7 +244,7 @@ __device__ __forceinline__ void load_u64(const uint64_t* base, uint32_t glast, c
 
 // Bound by VALU issue like the merge above.  Launch average of a sort, against
 // blocks of 64-bit keys in their own order (a compare and four selects per
-// compare-exchange): 10^8 keys 943 -> 622 us; 33,554,467 pairs 674 -> 292 us.
+// compare-exchange): 10^8 keys 943 -> 567 us; 33,554,467 pairs 674 -> 277 us.
 template <int EM, uint32_t TOUT, int W, bool PAIRS>
 __global__ __launch_bounds__(W * 64, EM == 16 ? 4 : 6) void k_merge64(Phase64 ph, Bufs64 b, RoundArgs ra,
                                                                       const uint32_t* __restrict__ table,
@@ -419,12 +420,15 @@ hipError_t launch_merge_pairs(const Phase& ph, const Bufs& b, const RoundArgs& r
                               uint32_t flip, hipStream_t s) {
     if (ph.tiles == 0) return hipSuccess;
     if (ra.Tout > kToutPairs || ra.Tout % 4 || ra.K > kMaxFanout || ra.L < 128) return hipErrorInvalidValue;
-    // Up to as many tiles as are resident at once, one workgroup's latency is
-    // what counts, and eight waves of 128-word blocks take half as long over a
-    // level: 3.0e5 uniform pairs 79.1 us with the larger blocks and 71.1 with
-    // these, 2e6 pairs (521 tiles) 136 and 130, 4e6 (1042) 210 and 204.  Past
-    // that the larger blocks' fewer instructions win: 1e7 pairs 409 us and 416,
-    // 1e8 3.97 ms and 4.19.
+    // While a launch's tiles are resident at once, one workgroup's latency is what
+    // counts, and eight waves of 128-word blocks take half as long over a level;
+    // three such workgroups fit a compute unit (768 tiles at once), four of the
+    // larger blocks (1024).  Sorts with these and with the larger blocks: 300 tiles
+    // 102 and 108 us, 640 134 and 140; 768 147 and 144, 960 161 and 153 (a second
+    // wave of workgroups here, one there); 1024 168 and 173, 1300 198 and 205;
+    // 2048 the same.  Past that the larger blocks' fewer instructions win: 2605
+    // tiles 332 and 327, 28000 3540 and 3339.  The line lies at the larger blocks'
+    // residency.
     if (ph.tiles <= 1024)
         hipLaunchKernelGGL((k_merge_pairs<8, kToutPairs, 8>), dim3((unsigned)ph.tiles), dim3(8 * 64), 0, s, ph, b, ra,
                            table, flip);
@@ -437,8 +441,9 @@ hipError_t launch_merge_pairs(const Phase& ph, const Bufs& b, const RoundArgs& r
 template <bool PAIRS>
 static hipError_t launch64(const Phase64& ph, const Bufs64& b, const RoundArgs& ra, const uint32_t* table,
                            uint64_t flip, hipStream_t s) {
-    // as for the 32-bit pairs: eight waves of smaller blocks while one
-    // workgroup's latency counts
+    // as for the 32-bit pairs (the same workgroups fit): keys 300 tiles 92 and 98
+    // us, 960 158 and 157, 1300 196 and 199, 5000 635 and 613, 28000 3490 and 3320;
+    // pairs 99 and 108, 190 and 181, 234 and 244, 829 and 823, 4409 and 4265
     if (ph.tiles <= 1024)
         hipLaunchKernelGGL((k_merge64<8, kTout64, 8, PAIRS>), dim3((unsigned)ph.tiles), dim3(8 * 64), 0, s, ph, b, ra,
                            table, flip);

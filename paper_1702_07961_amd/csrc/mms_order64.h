@@ -184,7 +184,6 @@ __device__ __forceinline__ void store_by_tags(uint64_t* out, const uint64_t* E, 
             *reinterpret_cast<gu64x2*>(g + 2u * c) = u64x2{E[w & 0xFFFFu] ^ x, E[w >> 16] ^ x};
         } else {
             g[2u * c] = E[w & 0xFFFFu] ^ x;
-            if (2u * c + 1u < cnt) g[2u * c + 1u] = E[w >> 16] ^ x;
         }
     }
 }

@@ -19,10 +19,12 @@
 //
 // In LDS a 32-bit word i sits at i + (i >> 5) + (i >> 10): index bit i has the
 // bank weight 2^(i mod 5), and lane bits 0..4 of every layout are index bits of
-// different weights, so all accesses are free of bank conflicts.  For 64-bit
-// words the writes decide (16 lanes at a time over 32 banks; 6.1 cycles for 64
-// lanes against 8.2 with two lanes on a bank, while 64-bit reads take 2.5 either
-// way): i + (i >> 4) + (i >> 8) + (i >> 12) gives weights 2^(i mod 4), and lane
+// different weights, so all accesses are free of bank conflicts (the counter reads
+// zero).  For 64-bit words the writes decide (16 lanes at a time over 32 banks; 6.1
+// cycles for 64 lanes against 8.2 with two lanes on a bank, while 64-bit reads take
+// 2.5 either way; the counter reads 1.1 cycles an LDS instruction of the pairs' base
+// case, its gather by tag among them, and 1.9 with stride-64 keys),
+// and i + (i >> 4) + (i >> 8) + (i >> 12) gives weights 2^(i mod 4), and lane
 // bits 0..3 are index bits of different ones.  A word's address is the sum of
 // its lane's and its register's, the latter a constant.
 //
@@ -232,7 +234,7 @@ __device__ __forceinline__ void net_wave_step(typename Wd::T* X, typename Wd::T 
     net_regs<Wd, S < 8 ? S - 5 : 3, 0>(m);
 }
 
-// Steps 11 .. 14, the whole workgroup.
+// Steps 11 .. 13, the whole workgroup.
 template <class Wd, int S>
 __device__ __forceinline__ void net_tile_step(typename Wd::T* X, typename Wd::T (&m)[kNetRegs], uint32_t l, uint32_t w) {
     using T = typename Wd::T;
@@ -250,7 +252,6 @@ __device__ __forceinline__ void net_tile_step(typename Wd::T* X, typename Wd::T 
     lds_barrier();
     net_get<NetA<T>, 0>(X, m, l, w);
     lds_wave_sync();
-    if constexpr (S > 13) net_lanes<Wd, kXor2, false>(m, (l & 2u) != 0);
     if constexpr (S > 12) net_lanes<Wd, kXor1, false>(m, (l & 1u) != 0);
     net_regs<Wd, S < 12 ? S - 9 : 3, 0>(m);
 }
@@ -262,7 +263,7 @@ __device__ __forceinline__ void net_tile_step(typename Wd::T* X, typename Wd::T 
 template <class Wd, int W>
 __device__ __forceinline__ void net_sort(typename Wd::T* X, typename Wd::T (&m)[kNetRegs], uint32_t cnt, int lane,
                                          int wave) {
-    static_assert(W == 1 || W == 2 || W == 4 || W == 8 || W == 16, "whole wave bits");
+    static_assert(W == 1 || W == 2 || W == 4 || W == 8, "whole wave bits");
     const uint32_t l = (uint32_t)lane, w = (uint32_t)wave;
     if (w * 1024u < cnt) {
         net_reg_step<Wd, 1>(m);
@@ -285,8 +286,6 @@ __device__ __forceinline__ void net_sort(typename Wd::T* X, typename Wd::T (&m)[
         if (cnt > 2048u) net_tile_step<Wd, 12>(X, m, l, w);
     if constexpr (W >= 8)
         if (cnt > 4096u) net_tile_step<Wd, 13>(X, m, l, w);
-    if constexpr (W >= 16)
-        if (cnt > 8192u) net_tile_step<Wd, 14>(X, m, l, w);
 }
 
 // From layout A to the order of memory, inside the wave: register 4c + q of

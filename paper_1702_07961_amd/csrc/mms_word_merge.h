@@ -11,7 +11,9 @@
 // Work is planned in items, an item being up to 252 (124) consecutive outputs
 // of one pair of runs.  Everything is counted in chunks of two words (16 bytes):
 // runs start and end on chunks (the slots past a piece hold the sentinel), so
-// every LDS access of a block is one conflict-free 128-bit access per lane.
+// every LDS access of a block is one 128-bit access per lane at consecutive
+// chunks.  A wave's four rows start wherever their items do, so they may meet in
+// the banks: 23 to 27 % of the pair merge's LDS cycles, by input.
 // A level is merged in place: every row reads its item into registers, the
 // workgroup meets, and the sorted items go back to the slots they came from.
 // One buffer instead of two is what lets four workgroups share a compute
